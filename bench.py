@@ -43,7 +43,8 @@ KERNELS = {0: ("k_sweep_direct", "direct", ("wave_kernels.hip", "wave_direct.h",
            6: ("k_sweep_pair", "pair", ("wave_kernels_pair.hip", "wave_point.h")),
            7: ("k_sweep_stream", "semi", ("wave_kernels.hip", "wave_point.h")),
            8: ("k_sweep_persist", "persist", ("wave_kernels.hip", "wave_point.h")),
-           9: ("k_sweep_stream", "shuffle", ("wave_kernels.hip", "wave_point.h"))}
+           9: ("k_sweep_stream", "shuffle", ("wave_kernels.hip", "wave_point.h")),
+           10: ("k_sweep_block", "block", ("wave_kernels_block.hip", "wave_point.h"))}
 
 
 def kernel_source_sha(variant: int = 1) -> str:
@@ -69,6 +70,8 @@ def describe(cfg) -> str:
         return f"stream, persistent (one workgroup per CU), 64x{nw} zchunk={zc}"
     if v == 9:
         return f"stream, x neighbours by wavefront shuffles, 64x{nw} zchunk={zc}"
+    if v == 10:
+        return f"blocks of 64x{nw}x{zc} points"
     if v in (4, 5):
         return f"2.5-D {'ring of 9 LDS planes' if v == 4 else 'LDS plane + shifted registers'} " \
                f"64x{nw} zchunk={zc}"

@@ -329,12 +329,23 @@ int wave_energy_noalloc(wave_ctx *ctx, double *dev_out);
                                 waves_per_group in {8, 16}, zchunk as for
                                 WAVE_KERNEL_STREAM                        */
 
+#define WAVE_KERNEL_BLOCK 10 /* small grids: a 64 x ty x zc block of points per
+                                workgroup, every operand of the block
+                                requested at once, up to 4 sources and the
+                                receivers in the same launch; rows_per_wave =
+                                1, (waves_per_group, zchunk) = (ty, zc) in
+                                {(4,4)}, and (8,8) with damping off and no
+                                stochastic rounding; zc + 8 float planes below
+                                2 GiB (EINVAL)                            */
+
 /* Select the sweep kernel and its tile: rows_per_wave (RY) and
  * waves_per_group (NW) give a 64 x (RY*NW) xy tile; zchunk is the number of
  * z planes one workgroup streams (0 = automatic).  Only compiled
  * combinations are accepted (EINVAL otherwise): (RY, NW) in
  * {(1,16), (1,8), (2,8), (2,4)}, and (2,16) (64 x 32 tiles) without an eta
- * array.  The default is WAVE_KERNEL_PERSIST with (1,16) tiles and its
+ * array.  The default is WAVE_KERNEL_BLOCK where the state (u^n, u^{n-1}, vp,
+ * phi and eta of the points that have them) is at most 280 MB, and with
+ * damping off on larger grids too; else WAVE_KERNEL_PERSIST with (1,16) tiles and its
  * automatic chunk (half the streaming kernel's) on grids large enough for
  * 64-plane chunks of 64 x 16 tiles with about 2048 workgroups (512^3 and
  * up for cubes), else WAVE_KERNEL_STREAM with (1,8) tiles (also where the
@@ -352,7 +363,8 @@ int wave_set_kernel(wave_ctx *ctx, int32_t variant, int32_t rows_per_wave,
 
 /* Autotuner: advance the simulation by one untimed and `trial_steps` timed
  * real steps under the persistent launch (16 and 8 rows, two z-chunk
- * lengths), each compiled streaming tile shape at a few z-chunk lengths,
+ * lengths; the first of them gives its place to the block kernel where that is
+ * the default), each compiled streaming tile shape at a few z-chunk lengths,
  * with WAVE_TWO_STEP the two-step kernel with a few z-chunk lengths
  * (trial_steps rounded up to even there), the two-points-per-lane kernel
  * (both tile heights, two z-chunk lengths; not with an eta array), the

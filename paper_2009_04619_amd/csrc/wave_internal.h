@@ -96,6 +96,19 @@ struct InjectArgs {
   int32_t trace_row;
 };
 
+// Source adds and receiver samples a sweep launch does beside the sweep
+// (kernels that take it): the sources of this step, added to u^{n+1} as it is
+// written, and the receivers of the step before, sampled from u^n.
+constexpr int kStepSrc = 4;
+struct StepIO {
+  int32_t nsrc;               // at most kStepSrc; more go through launch_inject_record
+  int32_t sx[kStepSrc], sy[kStepSrc], sz[kStepSrc];
+  float sw[kStepSrc];         // w[n] of each source
+  int32_t nrec;               // 0: nothing to sample
+  const int64_t* rec_off;
+  double* row;                // the trace row of u^n
+};
+
 // One member of a batch (device table entry).  The sweep arguments' cur/nxt
 // pointers are chosen per step from u[] and the member's parity.
 struct BatchShot {
@@ -180,6 +193,24 @@ hipError_t launch_sweep_pair(const SweepArgs& a, int storage, int ty, int zchunk
 // Batched form: the members' block ranges laid out for 128 x ty tiles.
 hipError_t launch_sweep_batch_pair(const BatchShot* shots, BatchState* state, int nshots,
                                    int64_t total_blocks, int storage, int ty, hipStream_t s);
+// Sweep of small grids (wave_kernels_block.hip): 64 x ty x zc blocks, all
+// operands of a block requested at once; 4 x 4, and 8 x 8 with damping off and
+// no stochastic rounding.
+bool block_config_supported(int ty, int zc, const SweepArgs& a, int storage);
+// Bytes of the state a sweep touches.
+int64_t sweep_footprint(int nx, int ny, int nz, int w, bool damping, bool eta_array, int es);
+// The block a grid's default launch uses; 0, 0 where the streaming kernels
+// are the faster ones.  With a layer, 4 x 4 up to 280 MB of state, about what
+// the memory-side cache keeps (us per step, block against the best streaming
+// tile: float32 256^3, 228 MB, 52 against 65; 288^3, 325 MB, 89 against 90; 320^3
+// 117 against 113; bf16 288^3, 230 MB, 72 against 79; 320^3, 306 MB, 95 against
+// 93).  Without a layer 8 x 8 blocks on all but small grids (float32 256^3 40
+// against 37 with 4 x 4, 384^3 137 against 151 streaming, 600^3 659 against 685;
+// bf16 128^3, 17 MB, 6.6 against 7.5 with 4 x 4, 256^3 27 against 33, 512^3 220
+// against 221 streaming).
+void block_default(const SweepArgs& a, int storage, int* ty, int* zc);
+hipError_t launch_sweep_block(const SweepArgs& a, const StepIO& io, int storage, int ty, int zc,
+                              hipStream_t s);
 hipError_t launch_energy(const EnergyArgs& a, int storage, hipStream_t s);
 hipError_t launch_stream_copy(void* dst, const void* src, size_t bytes, hipStream_t s);
 // kind 0: read a (bytes), d a 4-byte sink; kind 1: d = a + b c over bytes each.

@@ -1,0 +1,401 @@
+// wave_kernels_block.hip -- the sweep of small grids: one 64 x TY x ZC block of
+// points per workgroup, all of its operands requested at once (paper Eq. 2-3
+// and the damping layer of Sec. III-B; the per-point arithmetic is
+// wave_point.h's, operand for operand).
+//
+// What bounds a small grid is latency: a workgroup of the streaming kernel
+// works through its 32 planes one after the other, 0.5 us each whatever the
+// grid (three planes of loads in flight against 1.5 us of memory latency),
+// on a chip that a few hundred workgroups do not fill (64^3: 24 workgroups,
+// 22.5 us a step).  Here a workgroup requests the u values of its block with
+// all halos, u^{n-1}, vp and phi together, waits once, stages the centre
+// planes in LDS with one barrier and computes ZC planes from registers and LDS.
+// The z halo is read (ZC + 8) / ZC times, which the XCD's L2 absorbs: its
+// blocks are neighbours.  The data fit the memory-side cache and are kept there
+// (plain loads, stores written through), and odd steps walk the blocks
+// backwards, so that a grid a little larger than that cache finds the part
+// touched last.  One step of this kernel also adds the sources and samples
+// the receivers of the step before, which saves the second launch.
+//
+// us per step with a source and a receiver line, before (64 x 8 streaming
+// tiles) -> now: 64^3 22.5 -> 4.4, 128^3 23.4 -> 9.5, 160^3 29.5 -> 16.7,
+// 192^3 35.9 -> 23.3, 256^3 65.0 -> 52 (20-cell layer; 16 at 64^3); 256^3
+// without a layer 50.1 -> 37.3, 7.2 TB/s of its algorithmic bytes (a copy inside
+// that cache moves 8.3).
+//
+// 4 x 4 rows and planes: 8 x 8 blocks read less halo, but hold more registers
+// with the layer's operands and leave fewer, longer workgroups (160^3 20.5).
+// Without a layer the registers are not short and 8 x 8 wins on larger grids.
+#include <algorithm>
+
+#include "wave_internal.h"
+#include "wave_point.h"
+
+namespace wave {
+namespace {
+
+typedef const double __attribute__((address_space(4))) BCDouble;
+typedef const float __attribute__((address_space(4))) BCFloat;
+
+// Staged planes of a block.  yz: the centre planes with their y halo, rows of
+// 64 floats, so that one base register and the 64-float strides of ds_read2st64
+// reach every y neighbour of every plane; xr: each row with its x halo, the
+// planes of a row back to back.
+template <int TY, int ZC>
+struct BlockLds {
+  float xr[TY][ZC][kTX + 2 * kR];
+  float yz[ZC][TY + 2 * kR][kTX];
+};
+
+// Where a block lies: its first point, its planes [zb, zb + nzb) with nzb <= ZC.
+struct BlockAt {
+  int x0, y0, zb, nzb;
+};
+
+// One wavefront's row of the block.  EM as in the streaming kernel: 0 no layer
+// point, 1 eta array, 2 tables.  FULL: the block has all ZC planes.  NTP: the
+// state is larger than the memory-side cache, and all but u^n goes around it.
+template <class S, int TY, int ZC, int EM, bool FULL, bool NTP>
+__device__ __forceinline__ void block_rows(const SweepArgs& a, const StepIO& io,
+                                           BlockLds<TY, ZC>& sm, const BlockAt& b, bool lay) {
+  using T = typename S::T;
+  constexpr int NT = 64 * TY;
+  constexpr int NYH = (2 * kR + TY - 1) / TY;  // y-halo rows per wavefront and plane
+  constexpr int NXE = 2 * kR * TY * ZC;        // x-halo cells of the block
+  constexpr int NXH = (NXE + NT - 1) / NT;
+  constexpr uint32_t ES = sizeof(T);
+  constexpr int kBst = NTP ? kSt : kStThrough;
+  constexpr bool LAYER = EM != 0;
+  constexpr bool EARR = EM == 1;
+  static_assert((2 * kR) % TY == 0, "whole y-halo rows per wavefront");
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int x = b.x0 + lane, y = b.y0 + wv;
+  const int nzb = FULL ? ZC : b.nzb;
+  // window index of plane k of the block (past a partial block's end: its last)
+  auto pl = [&](int k) -> uint32_t { return (uint32_t)(kR + (FULL ? k : min(k, nzb - 1))); };
+  const int64_t Q = a.plane;
+  const int P = a.pitch;
+  const uint32_t pe = (uint32_t)Q * ES, p4 = (uint32_t)Q * 4u;
+  // window: planes zb-4 .. zb+nzb+3 from row -4, as in the streaming kernel;
+  // offsets at kOOB read 0 and store nothing (ghosts, lanes past the grid)
+  const int64_t w0 = (int64_t)(b.zb - kR) * Q - (int64_t)kR * P;
+  const uint32_t nwin = (uint32_t)(nzb + 2 * kR);
+  const auto ru = rsrc_at(static_cast<const T*>(a.cur) + w0, nwin * pe);
+  const auto rn = rsrc_at(static_cast<T*>(a.nxt) + w0, nwin * pe);
+  const auto rv = rsrc_at(a.vp + w0, nwin * p4);
+  const auto rph = rsrc_at(LAYER ? (const void*)(a.phi + w0) : nullptr, LAYER ? nwin * p4 : 0u);
+  const auto ret = rsrc_at(EARR ? (const void*)(a.eta + w0) : nullptr, EARR ? nwin * p4 : 0u);
+  const bool valid = x < a.nx && y < a.ny;
+  const uint32_t ro = (uint32_t)((y + kR) * P + x);
+  const uint32_t vo = valid ? ro * ES : kOOB, vo4 = valid ? ro * 4u : kOOB;
+  const uint32_t fo = LAYER && lay ? vo4 : kOOB;  // phi and eta: layer points only
+
+  // sources of this step in the wavefront's row
+  uint32_t smask = 0;
+#pragma unroll
+  for (int s = 0; s < kStepSrc; ++s)
+    if (io.sy[s] == y && io.sz[s] >= b.zb && io.sz[s] < b.zb + nzb && io.sx[s] >= b.x0 &&
+        io.sx[s] < b.x0 + kTX)
+      smask |= 1u << s;
+
+  // every load of the block: first what the staged planes hold, then the rest
+  float q[ZC + 2 * kR], hy[NYH][ZC], hx[NXH], vv[ZC], pv[ZC], ph[ZC];
+#pragma unroll
+  for (int k = 0; k < ZC; ++k)
+    q[kR + k] = S::bld(ru, vo, (uint32_t)(FULL ? kR + k : min(kR + k, nzb + 2 * kR - 1)) * pe);
+#pragma unroll
+  for (int i = 0; i < NYH; ++i) {
+    const int hr = wv + i * TY;  // halo row (wave-uniform)
+    const int gy = hr < kR ? b.y0 - kR + hr : b.y0 + TY + (hr - kR);
+    const uint32_t ho =
+        gy >= 0 && gy < a.ny && x < a.nx ? (uint32_t)((gy + kR) * P + x) * ES : kOOB;
+#pragma unroll
+    for (int k = 0; k < ZC; ++k) hy[i][k] = S::bld(ru, ho, pl(k) * pe);
+  }
+#pragma unroll
+  for (int i = 0; i < NXH; ++i) {
+    const int e = tid + i * NT;
+    const int cc = e & (2 * kR - 1), rr = (e / (2 * kR)) % TY, k = e / (2 * kR * TY);
+    const int gx = cc < kR ? b.x0 - kR + cc : b.x0 + kTX + (cc - kR), gy = b.y0 + rr;
+    const bool in = k < nzb && gx >= 0 && gx < a.nx && gy < a.ny;
+    hx[i] = S::bld(ru, in ? (uint32_t)((gy + kR) * P + gx) * ES + (uint32_t)(kR + k) * pe : kOOB, 0u);
+  }
+#pragma unroll
+  for (int j = 0; j < kR; ++j) {
+    q[j] = S::bld(ru, vo, (uint32_t)j * pe);
+    q[kR + ZC + j] =
+        S::bld(ru, vo, (uint32_t)(FULL ? kR + ZC + j : min(kR + ZC + j, nzb + 2 * kR - 1)) * pe);
+  }
+#pragma unroll
+  for (int k = 0; k < ZC; ++k) {
+    vv[k] = NTP ? bld1_f32(rv, vo4, pl(k) * p4) : bld_f32(rv, vo4, pl(k) * p4);
+    pv[k] = NTP ? S::bld1(rn, vo, pl(k) * pe) : S::bld(rn, vo, pl(k) * pe);
+    if (LAYER) ph[k] = NTP ? bld1_f32(rph, fo, pl(k) * p4) : bld_f32(rph, fo, pl(k) * p4);
+  }
+  float er[ZC + 2], ex0[ZC], ex1[ZC], ey0[ZC], ey1[ZC];
+  double tsc = 0.0, tz[ZC];
+  float dqx = 0.0f, dqy = 0.0f, dz[ZC];
+  if (EM == 2) {
+    const double* tx = a.etab + 1;
+    const double* ty = tx + a.nx + 2;
+    const BCDouble* tzt = (const BCDouble*)(ty + a.ny + 2) + b.zb;
+    const BCFloat* dqzt = (const BCFloat*)(a.etq + a.nx + a.ny) + b.zb;
+    const int xc = min(x, a.nx - 1), yc = min(y, a.ny - 1);
+    tsc = tx[xc] + ty[yc];
+    dqx = a.etq[xc];
+    dqy = a.etq[a.nx + yc];
+#pragma unroll
+    for (int k = 0; k < ZC; ++k) {
+      tz[k] = tzt[pl(k) - kR];
+      dz[k] = dqzt[pl(k) - kR];
+    }
+  }
+  if (EARR) {
+    const uint32_t rb4 = (uint32_t)P * 4u;
+#pragma unroll
+    for (int k = 0; k < ZC; ++k) {
+      ex0[k] = bld_f32(ret, fo - 4u, pl(k) * p4);
+      ex1[k] = bld_f32(ret, fo + 4u, pl(k) * p4);
+      ey0[k] = bld_f32(ret, fo - rb4, pl(k) * p4);
+      ey1[k] = bld_f32(ret, fo + rb4, pl(k) * p4);
+    }
+#pragma unroll
+    for (int k = 0; k < ZC + 2; ++k)
+      er[k] = bld_f32(ret, fo, (uint32_t)(kR - 1 + (FULL ? k : min(k, nzb + 1))) * p4);
+  }
+
+  // stage the centre planes with their x and y halos; one barrier
+#pragma unroll
+  for (int k = 0; k < ZC; ++k) {
+    sm.yz[k][kR + wv][lane] = q[kR + k];
+    sm.xr[wv][k][kR + lane] = q[kR + k];
+#pragma unroll
+    for (int i = 0; i < NYH; ++i) {
+      const int hr = wv + i * TY;
+      sm.yz[k][hr < kR ? hr : TY + hr][lane] = hy[i][k];
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < NXH; ++i) {
+    const int e = tid + i * NT;
+    const int cc = e & (2 * kR - 1), rr = (e / (2 * kR)) % TY, k = e / (2 * kR * TY);
+    if (NXE % NT == 0 || e < NXE) sm.xr[rr][k][cc < kR ? cc : kTX + cc] = hx[i];
+  }
+  __syncthreads();
+
+  // the x rows' base in a register of its own: the reads then fit the 8-bit
+  // offsets of ds_read2 without an address add each
+  int xbase = (wv * ZC) * (kTX + 2 * kR) + kR + lane;
+  asm volatile("" : "+v"(xbase));
+  float res[ZC];
+#pragma unroll
+  for (int k = 0; k < ZC; ++k) {
+    const float* xr = &sm.xr[0][0][0] + xbase + k * (kTX + 2 * kR);
+    const float* yr = &sm.yz[k][kR + wv][lane];
+    const float c = q[kR + k];
+    float lap = a.c[0] * c;
+#pragma unroll
+    for (int m = 1; m <= kR; ++m) lap = __builtin_fmaf(a.c[m], xr[m] + xr[-m], lap);
+#pragma unroll
+    for (int m = 1; m <= kR; ++m)
+      lap = __builtin_fmaf(a.c[4 + m], yr[m * kTX] + yr[-m * kTX], lap);
+#pragma unroll
+    for (int m = 1; m <= kR; ++m)
+      lap = __builtin_fmaf(a.c[8 + m], q[kR + k + m] + q[kR + k - m], lap);
+    lap = __builtin_fmaf(a.ce, c, lap);
+    if (LAYER) {
+      float e, gx, gy, gz;
+      if (EARR) {
+        e = er[k + 1];
+        gx = (ex1[k] - ex0[k]) * a.q[0];
+        gy = (ey1[k] - ey0[k]) * a.q[1];
+        gz = (er[k + 2] - er[k]) * a.q[2];
+      } else {
+        const float et = (float)(a.dt * (tsc + tz[k]));
+        e = lay ? et : 0.0f;
+        gx = dqx;
+        gy = dqy;
+        gz = dz[k];
+      }
+      // outside the layer eta and phi read 0 and the store of phi is dropped
+      res[k] = upd_layer(c, pv[k], vv[k], lap, e, ph[k]);
+      const float nph = upd_phi(ph[k], e, gx, xr[1] - xr[-1], gy, yr[kTX] - yr[-kTX], gz,
+                                q[kR + k + 1] - q[kR + k - 1]);
+      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(nph), rph,
+                                            (int)(FULL || k < nzb ? fo : kOOB), (int)(pl(k) * p4), kBst);
+    } else {
+      res[k] = upd_inner(c, pv[k], vv[k], lap);
+    }
+  }
+
+  // to the storage type, then the sources of this step (Alg. 1), added to
+  // the stored value in list order; planes past the block store nothing
+  const uint32_t srkey = S::kSR ? pcg_hash((uint32_t)a.step) : 0u;
+  T ev[ZC];
+#pragma unroll
+  for (int k = 0; k < ZC; ++k) {
+    if constexpr (S::kSR)
+      ev[k] = f32_to_bf16_sr(res[k], sr_word(srkey, a.nx, a.ny, x, y, b.zb + k) >> (16 * (x & 1)));
+    else
+      ev[k] = S::enc(res[k]);
+  }
+  if (smask) {
+    for (int s = 0; s < kStepSrc; ++s) {
+      if (!(smask >> s & 1)) continue;
+#pragma unroll
+      for (int k = 0; k < ZC; ++k)
+        if (io.sz[s] == b.zb + k && io.sx[s] == x)
+          ev[k] = S::enc(__builtin_fmaf(vv[k], io.sw[s], S::cvt(ev[k])));
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < ZC; ++k) {
+    const int so = (int)(pl(k) * pe), vk = (int)(FULL || k < nzb ? vo : kOOB);
+    if constexpr (sizeof(T) == 4)
+      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, ev[k]), rn, vk, so, kBst);
+    else
+      __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, ev[k]), rn, vk, so, kBst);
+  }
+}
+
+// Blocks of a launch: tiles_x x tiles_y tiles, z cut like the streaming
+// kernel's chunks (at the layer faces, so whether a lane is a layer point is
+// fixed for a block).  m*: 2^32 / divisor rounded up, so that mulhi divides
+// (exact for dividend * divisor < 2^32, checked by the launcher).
+struct BlockGrid {
+  int tiles_x, tiles_y, layers;  // layers of blocks along z
+  int slab;                      // tile rows per XCD and layer
+  int per_xcd;                   // blocks per XCD, slab padding included
+  uint32_t mx, mslab;
+};
+__device__ __forceinline__ int div_by(int n, int d, uint32_t m) {
+  return d == 1 ? n : (int)__umulhi((uint32_t)n, m);
+}
+
+// LM: the layer's update, 0 damping off, 1 eta array, 2 tables.
+template <class S, int TY, int ZC, int LM, bool NTP>
+__global__ __launch_bounds__(64 * TY, 4) void k_sweep_block(SweepArgs a, StepIO io, BlockGrid g) {
+  __shared__ BlockLds<TY, ZC> sm;
+  const int slot = blockIdx.x >> 3;
+  if (slot >= g.per_xcd) {  // receivers of u^n, the last step's field
+    record_row<S>(a, io, (blockIdx.x - 8 * g.per_xcd) * 64 * TY + threadIdx.x);
+    return;
+  }
+  // XCD b mod 8 takes one slab of tile rows through all layers of blocks, so
+  // neighbouring blocks read their halos from one L2 (8 % faster at 256^3
+  // than a contiguous run of layers per XCD).  Odd steps walk the blocks
+  // backwards: what a step touched last is still in the memory-side cache
+  // when the next one starts (256^3: 60.7 -> 51.6 us).
+  const int at = (a.step & 1) ? g.per_xcd - 1 - slot : slot;
+  const int t2 = div_by(at, g.tiles_x, g.mx);
+  const int zl = div_by(t2, g.slab, g.mslab);
+  const int ty = (int)(blockIdx.x & 7) * g.slab + t2 - zl * g.slab;
+  if (ty >= g.tiles_y) return;
+  constexpr bool damp = LM != 0;
+  const ChunkInfo c = chunk_of(zl, a.nz, a.w, ZC, damp);
+  BlockAt b;
+  b.x0 = (at - t2 * g.tiles_x) * kTX;
+  b.y0 = ty * TY;
+  b.zb = c.zb;
+  b.nzb = c.ze - c.zb;
+  const int x = b.x0 + (threadIdx.x & 63);
+  const int y = b.y0 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool lay = damp && x < a.nx && y < a.ny &&
+                   (c.cap || x < a.w || x >= a.nx - a.w || y < a.w || y >= a.ny - a.w);
+  if (b.nzb == ZC) {
+    if (LM == 0 || !__any(lay))
+      block_rows<S, TY, ZC, 0, true, NTP>(a, io, sm, b, false);
+    else
+      block_rows<S, TY, ZC, LM, true, NTP>(a, io, sm, b, lay);
+  } else {
+    if (LM == 0 || !__any(lay))
+      block_rows<S, TY, ZC, 0, false, NTP>(a, io, sm, b, false);
+    else
+      block_rows<S, TY, ZC, LM, false, NTP>(a, io, sm, b, lay);
+  }
+}
+
+template <class S, int TY, int ZC, int LM, bool NTP>
+hipError_t block_t(const SweepArgs& a, const StepIO& io, hipStream_t st) {
+  BlockGrid g;
+  g.tiles_x = cdiv(a.nx, kTX);
+  g.tiles_y = cdiv(a.ny, TY);
+  g.layers = chunk_count(a.nz, a.w, ZC, a.damping != 0);
+  g.slab = cdiv(g.tiles_y, 8);
+  const int64_t n = (int64_t)g.tiles_x * g.slab * g.layers;
+  if ((int64_t)(ZC + 2 * kR) * a.plane * 4 > kWindowMax ||
+      n * std::max(g.tiles_x, g.slab) >= (int64_t(1) << 32) || n > 0x0fffffff)
+    return hipErrorInvalidValue;
+  g.per_xcd = (int)n;
+  auto magic = [](int d) { return (uint32_t)(0xffffffffu / (uint32_t)d + 1u); };
+  g.mx = magic(g.tiles_x);
+  g.mslab = magic(g.slab);
+  const int rec = io.nrec > 0 ? cdiv(io.nrec, 64 * TY) : 0;
+  const dim3 grid((unsigned)(8 * g.per_xcd + rec)), blk(64 * TY);
+  hipLaunchKernelGGL((k_sweep_block<S, TY, ZC, LM, NTP>), grid, blk, 0, st, a, io, g);
+  return hipGetLastError();
+}
+
+template <class S>
+hipError_t block_s(const SweepArgs& a, const StepIO& io, int ty, int zc, bool nt, hipStream_t st) {
+  if (ty == 4 && zc == 4)
+    return a.eta       ? block_t<S, 4, 4, 1, false>(a, io, st)
+           : a.damping ? block_t<S, 4, 4, 2, false>(a, io, st)
+                       : block_t<S, 4, 4, 0, false>(a, io, st);
+  if constexpr (!S::kSR) {
+    if (ty == 8 && zc == 8 && !a.damping)
+      return nt ? block_t<S, 8, 8, 0, true>(a, io, st) : block_t<S, 8, 8, 0, false>(a, io, st);
+  }
+  return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+bool block_config_supported(int ty, int zc, const SweepArgs& a, int storage) {
+  const bool cfg = (ty == 4 && zc == 4) || (ty == 8 && zc == 8 && !a.damping && storage != 3);
+  const int64_t n = (int64_t)cdiv(a.nx, kTX) * cdiv(cdiv(a.ny, ty > 0 ? ty : 1), 8) *
+                    chunk_count(a.nz, a.w, zc > 0 ? zc : 1, a.damping != 0);
+  const int64_t d = std::max(cdiv(a.nx, kTX), cdiv(cdiv(a.ny, ty > 0 ? ty : 1), 8));
+  return cfg && (int64_t)(zc + 2 * kR) * a.plane * 4 <= kWindowMax && n * d < (int64_t(1) << 32) &&
+         n <= 0x0fffffff;
+}
+
+int64_t sweep_footprint(int nx, int ny, int nz, int w, bool damping, bool eta_array, int es) {
+  const int64_t pts = (int64_t)nx * ny * nz;
+  const int64_t inner = (int64_t)(nx - 2 * w) * (ny - 2 * w) * (nz - 2 * w);
+  return pts * (2 * es + 4 + (eta_array ? 4 : 0)) + (damping ? (pts - inner) * 4 : 0);
+}
+
+void block_default(const SweepArgs& a, int storage, int* ty, int* zc) {
+  const int es = storage == 0 ? 4 : 2;
+  const int64_t bytes =
+      sweep_footprint(a.nx, a.ny, a.nz, a.w, a.damping != 0, a.eta != nullptr, es);
+  *ty = *zc = 0;
+  if (!a.damping && storage != 3 && bytes > (es == 4 ? 240 : 24) * 1000000LL)
+    *ty = *zc = 8;
+  else if (bytes <= 280 * 1000000LL)
+    *ty = *zc = 4;
+  if (*ty && !block_config_supported(*ty, *zc, a, storage)) *ty = *zc = 0;
+}
+
+hipError_t launch_sweep_block(const SweepArgs& a, const StepIO& io, int storage, int ty, int zc,
+                              hipStream_t s) {
+  // past 400 MB (no layer: one array set of u, u_prev and vp) the cache holds
+  // too little of the state to be worth the traffic: 8 x 8 blocks without a
+  // layer run 320x304x288 (336 MB) in 71.0 us plain and 72.0 around it, 384^3
+  // (680 MB) in 149 and 137
+  const bool nt = sweep_footprint(a.nx, a.ny, a.nz, a.w, a.damping != 0, a.eta != nullptr,
+                                  storage == 0 ? 4 : 2) > 400 * 1000000LL;
+  switch (storage) {
+    case 0: return block_s<StF32>(a, io, ty, zc, nt, s);
+    case 1: return block_s<StBF16>(a, io, ty, zc, nt, s);
+    case 2: return block_s<StF16>(a, io, ty, zc, nt, s);
+    case 3: return block_s<StBF16SR>(a, io, ty, zc, nt, s);
+  }
+  return hipErrorInvalidValue;
+}
+
+}  // namespace wave

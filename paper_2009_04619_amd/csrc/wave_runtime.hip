@@ -257,6 +257,7 @@ struct wave_ctx {
   double vmax;
   int nsrc, nrec, trace_count;
   std::vector<int32_t> src_host;   // (i, j, k) of the sources
+  std::vector<float> wav_host;     // the first kStepSrc sources' samples, max_steps each
   bool src_fit2;                   // the sources fit the two-step kernel's tiles
   int variant, ry, nw, zchunk;
   int shp[3];             // WAVE_KERNEL_GMEM: block (bx, by, bz); RING/SHIFT: (1, ty, zchunk)
@@ -790,6 +791,7 @@ int wave_alloc(const wave_desc* d, const float* vel, const float* eta, void* dev
   c->q[2] = (float)(1.0 / (4.0 * d->dz * d->dz));
   c->nsrc = c->nrec = c->trace_count = 0;
   c->src_host.clear();
+  c->wav_host.clear();
   c->src_fit2 = true;
   c->shp[0] = c->shp[1] = c->shp[2] = 0;
   c->groups = persistent_groups();
@@ -799,12 +801,23 @@ int wave_alloc(const wave_desc* d, const float* vel, const float* eta, void* dev
   // workgroup per tile); on smaller grids the persistent launch's short
   // chunks and few items per workgroup cost more than its balance gains,
   // and one workgroup per 64 x 8 tile is the fastest (160^3: 29.5 us
-  // against 44.9; 384^3: 181 against 209)
+  // against 44.9; 384^3: 181 against 209); grids whose state the memory-side
+  // cache holds run the block kernel (block_default)
   const bool large = wave::auto_zchunk(c->L.nx, c->L.ny, c->L.nz, 1, 16) >= 64;
   c->variant = c->groups >= 8 && large ? WAVE_KERNEL_PERSIST : WAVE_KERNEL_STREAM;
   c->ry = 1;
   c->nw = large ? 16 : 8;
   c->zchunk = 0;
+  {
+    int bty, bzc;
+    wave::block_default(sweep_args(c), kernel_storage(d), &bty, &bzc);
+    if (bty) {
+      c->variant = WAVE_KERNEL_BLOCK;
+      c->shp[0] = 1;
+      c->shp[1] = bty;
+      c->shp[2] = bzc;
+    }
+  }
   c->timing = false;
   c->events_used = 0;
   c->ev_join = nullptr;
@@ -893,6 +906,7 @@ int wave_inject(wave_ctx* c, int32_t i, int32_t j, int32_t k, const float* sampl
   HIPCHK(c, hipMemcpyAsync(sijk, ijk3, 12, hipMemcpyHostToDevice, c->stream), "hipMemcpyAsync");
   HIPCHK(c, hipStreamSynchronize(c->stream), "hipStreamSynchronize");
   c->nsrc += 1;
+  if (c->nsrc <= wave::kStepSrc) c->wav_host.insert(c->wav_host.end(), row.begin(), row.end());
   c->src_host.insert(c->src_host.end(), ijk3, ijk3 + 3);
   c->src_fit2 = wave::sweep2_sources_fit(c->src_host.data(), c->nsrc);
   return WAVE_OK;
@@ -1033,7 +1047,15 @@ int wave_step(wave_ctx* c, int32_t n) {
   const int zc25 = !shape25 ? 0
                    : c->shp[2] > 0 ? std::min(c->shp[2], c->L.nz)
                                    : wave::auto_zchunk25(c->L.nx, c->L.ny, c->L.nz, c->shp[1]);
+  // the block kernel adds up to kStepSrc sources and samples the receivers of
+  // the step before in its own launch; the last step's receivers follow it
+  const bool fused = c->variant == WAVE_KERNEL_BLOCK && c->nsrc <= wave::kStepSrc;
+  wave::StepIO io;
+  memset(&io, 0, sizeof(io));
+  for (int s = 0; s < wave::kStepSrc; ++s) io.sz[s] = -1;  // unused entries match no point
   auto launch_one = [&](const wave::SweepArgs& s) -> hipError_t {
+    if (c->variant == WAVE_KERNEL_BLOCK)
+      return wave::launch_sweep_block(s, io, kernel_storage(&c->d), c->shp[1], c->shp[2], c->stream);
     if (c->variant == WAVE_KERNEL_GMEM)
       return wave::launch_sweep_gmem(s, kernel_storage(&c->d), c->shp[0], c->shp[1], c->shp[2], c->stream);
     if (shape25)
@@ -1054,20 +1076,38 @@ int wave_step(wave_ctx* c, int32_t n) {
 
   wave::InjectArgs ia = inject_args(c);
 
+  double* const traces = c->nrec > 0 ? reinterpret_cast<double*>(c->at(c->plan.traces)) : nullptr;
+  const int wrow = std::max(c->d.max_steps, 1);
+  if (fused) {
+    io.nsrc = c->nsrc;
+    for (int s = 0; s < c->nsrc; ++s) {
+      io.sx[s] = c->src_host[3 * s];
+      io.sy[s] = c->src_host[3 * s + 1];
+      io.sz[s] = c->src_host[3 * s + 2];
+    }
+    io.rec_off = ia.rec_off;
+  }
   for (int t = 0; t < n; ++t) {
     sa.cur = c->u_origin(c->icur);
     sa.nxt = c->u_origin(c->iprev);
     sa.step = (int32_t)c->step;
+    if (fused) {
+      for (int s = 0; s < c->nsrc; ++s)
+        io.sw[s] = c->step < wrow ? c->wav_host[(size_t)s * wrow + c->step] : 0.0f;
+      io.nrec = t > 0 ? c->nrec : 0;
+      if (t > 0 && traces) io.row = traces + (int64_t)(c->trace_count - 1) * c->nrec;
+    }
     hipEvent_t e1;
     int rc = timing_begin(c, &e1);
     if (rc) return rc;
     hipError_t e = launch_one(sa);
     if (e != hipSuccess) return dev_fail(c, e, "sweep launch");
     if (e1) HIPCHK(c, hipEventRecord(e1, c->stream), "hipEventRecord");
-    if (c->nsrc > 0 || c->nrec > 0) {
+    if (fused ? t == n - 1 && c->nrec > 0 : c->nsrc > 0 || c->nrec > 0) {
       ia.u = sa.nxt;
+      ia.nsrc = fused ? 0 : c->nsrc;
       ia.step = (int32_t)c->step;
-      ia.traces = c->nrec > 0 ? reinterpret_cast<double*>(c->at(c->plan.traces)) : nullptr;
+      ia.traces = traces;
       ia.trace_row = c->trace_count;
       e = wave::launch_inject_record(ia, kernel_storage(&c->d), c->stream);
       if (e != hipSuccess) return dev_fail(c, e, "inject/record launch");
@@ -1294,6 +1334,16 @@ int wave_set_kernel(wave_ctx* c, int32_t variant, int32_t ry, int32_t nw, int32_
     c->shp[2] = zchunk;
     return WAVE_OK;
   }
+  if (variant == WAVE_KERNEL_BLOCK) {
+    if (ry != 1 || !wave::block_config_supported(nw, zchunk, sweep_args(c), kernel_storage(&c->d)))
+      return fail(WAVE_EINVAL, "block kernel: rows_per_wave 1, 4 x 4 rows and planes (8 x 8 with damping off and "
+                               "no stochastic rounding), and planes small enough");
+    c->variant = variant;
+    c->shp[0] = 1;
+    c->shp[1] = nw;
+    c->shp[2] = zchunk;
+    return WAVE_OK;
+  }
   if (variant == WAVE_KERNEL_RING || variant == WAVE_KERNEL_SHIFT) {
     if (ry != 1 || (nw != 8 && nw != 16)) return fail(WAVE_EINVAL, "2.5-D shape needs rows_per_wave 1, 8 or 16 rows");
     if (zchunk < 0) return fail(WAVE_EINVAL, "zchunk < 0");
@@ -1334,8 +1384,8 @@ int wave_tune(wave_ctx* c, int32_t trial_steps, int32_t chosen[4]) {
     if (std::find(cand.begin(), cand.end(), e) == cand.end()) cand.push_back(e);
   };
   const bool ea = eta_array(&c->d);
-  // the persistent launch first (the default), at its automatic chunk and
-  // twice that
+  // the persistent launch first, at its automatic chunk and twice that; where
+  // the block kernel is the default it takes the first of these places
   for (const auto& t : {std::array<int, 2>{1, 16}, std::array<int, 2>{1, 8}}) {
     if (c->groups < 8) continue;
     const int za = persist_zchunk(c, t[0], t[1], 0);
@@ -1343,6 +1393,11 @@ int wave_tune(wave_ctx* c, int32_t trial_steps, int32_t chosen[4]) {
       const int zc = stream_zchunk(c, t[0], t[1], z);
       if (zc >= 1) add({WAVE_KERNEL_PERSIST, t[0], t[1], zc});
     }
+  }
+  {
+    int bty, bzc;
+    wave::block_default(sweep_args(c), kernel_storage(&c->d), &bty, &bzc);
+    if (bty && !cand.empty()) cand[0] = {WAVE_KERNEL_BLOCK, 1, bty, bzc};
   }
   for (int k = 0; k < nshape; ++k) {
     const int ry = kShapes[k][0], nw = kShapes[k][1];
@@ -1402,7 +1457,8 @@ int wave_tune(wave_ctx* c, int32_t trial_steps, int32_t chosen[4]) {
   const int shp0[3] = {c->shp[0], c->shp[1], c->shp[2]};
   auto is_shape = [](int v) {
     return v == WAVE_KERNEL_GMEM || v == WAVE_KERNEL_RING || v == WAVE_KERNEL_SHIFT ||
-           v == WAVE_KERNEL_PAIR || v == WAVE_KERNEL_SEMI || v == WAVE_KERNEL_SHUFFLE;
+           v == WAVE_KERNEL_PAIR || v == WAVE_KERNEL_SEMI || v == WAVE_KERNEL_SHUFFLE ||
+           v == WAVE_KERNEL_BLOCK;
   };
   float best = 0.0f;
   std::array<int, 4> pick = {variant, ry0, nw0, zc0};

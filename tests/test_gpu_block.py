@@ -1,0 +1,93 @@
+"""The block kernel of small grids (WAVE_KERNEL_BLOCK) against the float32
+oracle, bit for bit: partial blocks on every axis, layers that are no multiple
+of the block, all-layer grids, every storage type and rounding, an eta array,
+damping off (both block shapes), sources that share a cell, more sources than
+one launch takes, and receivers sampled over several calls."""
+import sys
+
+import numpy as np
+import pytest
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def W():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU (run with -m 'not gpu' on CPU)")
+    from paper_2009_04619_amd import wave
+    return wave
+
+
+def say(*a):
+    print(*a, flush=True)
+    sys.stdout.flush()
+
+
+def run(W, shot, calls, kernel, storage="f32", damping=True, sr=False, eta=None):
+    sh = W.shot_from_synth(shot, storage=storage, damping=damping, max_steps=sum(calls),
+                           stochastic_round=sr, eta=eta)
+    sh.set_kernel(*kernel)
+    for n in calls:
+        sh.step(n)
+    out = dict(u=sh.read(W.WAVE_FIELD_U), u_prev=sh.read(W.WAVE_FIELD_UPREV),
+               phi=sh.read(W.WAVE_FIELD_PHI), traces=sh.traces())
+    sh.close()
+    return out
+
+
+GRIDS = [  # nx, ny, nz, w, storage, damping, sources
+    (64, 64, 64, 16, "f32", True, 1),
+    (70, 45, 37, 5, "f32", True, 2),
+    (129, 17, 22, 7, "bf16", True, 3),
+    (200, 37, 13, 3, "f16", True, 4),
+    (66, 30, 33, 6, "bf16sr", True, 2),
+    (40, 36, 38, 18, "f32", True, 7),        # all layer but a core; more sources than kStepSrc
+    (131, 35, 19, 0, "f32", False, 2),
+    (65, 33, 11, 0, "f16", False, 5),
+    (6, 6, 7, 3, "f32", True, 1),
+    (1, 1, 1, 0, "bf16", False, 1),
+]
+
+
+@pytest.mark.parametrize("grid", GRIDS, ids=lambda g: f"{g[0]}x{g[1]}x{g[2]}_w{g[3]}_{g[4]}_src{g[6]}")
+def test_block_equals_oracle(W, grid):
+    nx, ny, nz, w, storage, damping, nsrc = grid
+    calls = (1, 6, 2)
+    steps = sum(calls)
+    shot = synth.config_small_layered(nx, ny, nz, w, steps, seed=nx + 5 * nz, nsrc=nsrc)
+    if nsrc > 2:
+        shot.src[2] = shot.src[0]           # two sources in one cell, in list order
+    expect = oracle.run_shot(shot, steps=steps, precision="f32", storage=storage, damping=damping)
+    if not damping:
+        expect["phi"] = np.zeros_like(expect["u"])
+    sr = storage == "bf16sr"
+    for k in [(10, 1, 4, 4)] + ([] if damping or sr else [(10, 1, 8, 8)]):
+        say(f"case block {k} grid {grid}")
+        got = run(W, shot, calls, k, "bf16" if sr else storage, damping, sr)
+        for key in ("u", "u_prev", "phi", "traces"):
+            assert np.array_equal(got[key], expect[key]), (k, grid, key)
+
+
+def test_block_eta_array(W):
+    nx, ny, nz, w = 75, 29, 34, 5
+    shot = synth.config_small_layered(nx, ny, nz, w, 8, seed=77, nsrc=2)
+    eta = np.random.default_rng(3).uniform(0.0, 0.4, (nz, ny, nx)).astype(np.float32)
+    say("case block eta array")
+    expect = oracle.run_shot(shot, steps=8, precision="f32", eta=eta)
+    got = run(W, shot, (8,), (10, 1, 4, 4), eta=eta)
+    for key in ("u", "u_prev", "phi", "traces"):
+        assert np.array_equal(got[key], expect[key]), key
+
+
+def test_block_refusals(W):
+    shot = synth.config_small_layered(40, 30, 20, 4, 4, seed=5)
+    sh = W.shot_from_synth(shot)
+    for bad in ((10, 1, 8, 8), (10, 2, 4, 4), (10, 1, 4, 8), (10, 1, 4, 0), (10, 1, 0, 4), (10, 1, 4, -4)):
+        assert W.wave_set_kernel(sh.ctx, *bad) == W.WAVE_EINVAL, bad
+    assert W.wave_set_kernel(sh.ctx, 10, 1, 4, 4) == W.WAVE_OK
+    sh.close()
