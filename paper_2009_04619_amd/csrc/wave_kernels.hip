@@ -661,7 +661,7 @@ __global__ __launch_bounds__(64 * NW, WAVE_STREAM_WPS(RY, NW)) void k_sweep_stre
   __shared__ float sm[2][LSZ];
 
   // XCD-aware tile order (tile_at)
-  const TileAt t = tile_at(blockIdx.x, tiles_x, tiles_y);
+  const TileAt t = tile_at(order_block(blockIdx.x, gridDim.x, a.step), tiles_x, tiles_y);
   if (t.ty >= tiles_y) return;
   const bool damp = a.damping != 0;
   const ChunkInfo c = chunk_of(t.ch, a.nz, a.w, zchunk, damp);
@@ -699,7 +699,7 @@ __global__ __launch_bounds__(64 * NW, WAVE_STREAM_WPS(RY, NW)) void k_sweep_pers
   for (int k = 0; k * G < items; ++k) {
     const int slot = k * G + (g + 5 * k) % G;
     if (slot >= items) continue;
-    const TileAt t = tile_at(8 * (int64_t)slot + xcd, tiles_x, tiles_y, 1);
+    const TileAt t = tile_at(order_block(8 * (int64_t)slot + xcd, 8 * (int64_t)items, a.step), tiles_x, tiles_y, 1);
     const ChunkInfo c = chunk_of(t.ch, a.nz, a.w, zchunk, damp);
     if (t.ty >= tiles_y || c.zb >= c.ze) continue;
     stream_tile<S, RY, NW, false, EA>(a, sm, t.tx * kTX, t.ty * TY, c.zb, c.ze, damp && c.cap);
@@ -718,7 +718,8 @@ __global__ __launch_bounds__(64 * NW, WAVE_STREAM_WPS(RY, NW)) void k_sweep_batc
   constexpr int TY = RY * NW;
   constexpr int LSZ = (TY + 2 * kR) * (kTX + 2 * kR) + 64;
   __shared__ float sm[2][LSZ];
-  const int64_t bid = blockIdx.x;
+  // every running member has taken the same number of steps in this run
+  const int64_t bid = order_block(blockIdx.x, gridDim.x, state[0].done);
   const int m = batch_member(shots, nshots, bid);
   const BatchShot& b = shots[m];
   const BatchState st = state[m];
