@@ -345,11 +345,13 @@ int wave_energy_noalloc(wave_ctx *ctx, double *dev_out);
  * {(1,16), (1,8), (2,8), (2,4)}, and (2,16) (64 x 32 tiles) without an eta
  * array.  The default is WAVE_KERNEL_BLOCK where the state (u^n, u^{n-1}, vp,
  * phi and eta of the points that have them) is at most 280 MB, and with
- * damping off on larger grids too; else WAVE_KERNEL_PERSIST with (1,16) tiles and its
- * automatic chunk (half the streaming kernel's) on grids large enough for
- * 64-plane chunks of 64 x 16 tiles with about 2048 workgroups (512^3 and
- * up for cubes), else WAVE_KERNEL_STREAM with (1,8) tiles (also where the
- * CU count cannot be queried).  The streaming
+ * damping off on larger grids too; else, with 16-bit storage and no eta array,
+ * WAVE_KERNEL_PAIR with 8 rows (with stochastic rounding 16 rows, and only on
+ * the large grids of the next clause); else WAVE_KERNEL_PERSIST with (1,16)
+ * tiles and its automatic chunk (half the streaming kernel's) on grids large
+ * enough for 64-plane chunks of 64 x 16 tiles with about 2048 workgroups
+ * (512^3 and up for cubes), else WAVE_KERNEL_STREAM with (1,8) tiles (also
+ * where the CU count cannot be queried).  The streaming
  * kernel addresses a chunk's planes with 32-bit offsets, so zchunk is cut
  * to what keeps zchunk + 8 float planes below 2 GiB; a grid whose single
  * plane is too large for that runs the direct kernel.  With

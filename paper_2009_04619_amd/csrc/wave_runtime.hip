@@ -811,11 +811,24 @@ int wave_alloc(const wave_desc* d, const float* vel, const float* eta, void* dev
   {
     int bty, bzc;
     wave::block_default(sweep_args(c), kernel_storage(d), &bty, &bzc);
+    // 16-bit storage moves half the bytes per instruction of a lane, so on
+    // grids past the block kernel's it runs two points per lane: 128 x 8 tiles
+    // (bf16, us per sweep, against the best one-point launch: 384^3 134 / 147,
+    // 512^3 286 / 321, 600^3 510 / 546, 1000 x 1000 x 256 649 / 691; 448^3 ties,
+    // 216 / 214).  With stochastic rounding the registers allow it only in
+    // 128 x 16 tiles, which win on large grids (512^3 327 / 354; 448^3 255 / 236)
+    const bool sr = kernel_storage(d) == 3;
+    const int pty = sr ? 16 : 8;
     if (bty) {
       c->variant = WAVE_KERNEL_BLOCK;
       c->shp[0] = 1;
       c->shp[1] = bty;
       c->shp[2] = bzc;
+    } else if (c->es == 2 && (large || !sr) && pair_zchunk(c, pty, 0) >= 1) {
+      c->variant = WAVE_KERNEL_PAIR;
+      c->shp[0] = 1;
+      c->shp[1] = pty;
+      c->shp[2] = 0;
     }
   }
   c->timing = false;
