@@ -366,7 +366,7 @@ int wave_set_kernel(wave_ctx *ctx, int32_t variant, int32_t rows_per_wave,
 /* Autotuner: advance the simulation by one untimed and `trial_steps` timed
  * real steps under the persistent launch (16 and 8 rows, two z-chunk
  * lengths; the first of them gives its place to the block kernel where that is
- * the default), each compiled streaming tile shape at a few z-chunk lengths,
+ * the default and WAVE_TWO_STEP is not set), each compiled streaming tile shape at a few z-chunk lengths,
  * with WAVE_TWO_STEP the two-step kernel with a few z-chunk lengths
  * (trial_steps rounded up to even there), the two-points-per-lane kernel
  * (both tile heights, two z-chunk lengths; not with an eta array), the

@@ -1399,6 +1399,7 @@ int wave_tune(wave_ctx* c, int32_t trial_steps, int32_t chosen[4]) {
   const bool ea = eta_array(&c->d);
   // the persistent launch first, at its automatic chunk and twice that; where
   // the block kernel is the default it takes the first of these places
+  // (not with WAVE_TWO_STEP, whose tuning compares the streaming shapes)
   for (const auto& t : {std::array<int, 2>{1, 16}, std::array<int, 2>{1, 8}}) {
     if (c->groups < 8) continue;
     const int za = persist_zchunk(c, t[0], t[1], 0);
@@ -1410,7 +1411,7 @@ int wave_tune(wave_ctx* c, int32_t trial_steps, int32_t chosen[4]) {
   {
     int bty, bzc;
     wave::block_default(sweep_args(c), kernel_storage(&c->d), &bty, &bzc);
-    if (bty && !cand.empty()) cand[0] = {WAVE_KERNEL_BLOCK, 1, bty, bzc};
+    if (bty && !cand.empty() && !two_step(&c->d)) cand[0] = {WAVE_KERNEL_BLOCK, 1, bty, bzc};
   }
   for (int k = 0; k < nshape; ++k) {
     const int ry = kShapes[k][0], nw = kShapes[k][1];
