@@ -417,8 +417,9 @@ int wave_stream_mix(int32_t kind, void *dst, const void *a, const void *b, const
 /* ---- many shots per launch (batching) ------------------------------------------ */
 
 /* A batch advances several contexts together: every time step is one sweep
- * launch covering all members (their tiles side by side in one grid) plus
- * one launch for all members' sources and receivers.  Each member takes the
+ * launch covering all members of a group (their tiles side by side in one grid;
+ * wave_batch_set_kernel says what a group is) plus one launch for their sources
+ * and receivers.  Each member takes the
  * same steps, with the same arithmetic, as under wave_step, so its results
  * are identical to a run on its own.  Members must share the batch's storage
  * type; their streams may differ from the batch's: the batch's launches
@@ -462,13 +463,20 @@ int wave_batch_remaining(const wave_batch *b, const wave_ctx *ctx, int32_t *rema
 /* Tile shape of the batch sweep (same combinations as wave_set_kernel, or
  * rows_per_wave = 0 for the two-points-per-lane kernel with 128 x
  * waves_per_group tiles, waves_per_group in {8, 16}; EINVAL while a member
- * holds an eta array, and such a member cannot join then) and the number of
- * steps captured into one graph (0 = plain launches). */
+ * holds an eta array, and such a member cannot join then), and the number of
+ * steps captured into one graph (0 = plain launches).  A batch starts without
+ * a set tile, and (4, 4) returns to that: each member's sweep is then chosen by
+ * its size.  Members that run WAVE_KERNEL_BLOCK by default, with at most 4
+ * sources, run it here; the others 64 x 8 tiles, or 128 x 8 with two points per
+ * lane (16-bit storage, no eta array, no stochastic rounding).  Block-kernel
+ * members whose states together fit the memory-side cache take their steps of a
+ * run together, one group of members after the other; their launches are never
+ * captured, and need no second launch for sources and receivers. */
 int wave_batch_set_kernel(wave_batch *b, int32_t rows_per_wave, int32_t waves_per_group);
 int wave_batch_set_graph(wave_batch *b, int32_t steps_per_graph);
 
-/* Autotuner for a batch: runs trial_steps steps under each compiled tile
- * shape (and the two-points-per-lane tiles when no member holds an eta
+/* Autotuner for a batch: runs trial_steps steps without a set tile and under
+ * each compiled tile shape but 64 x 8 in four wavefronts (and the two-points-per-lane tiles when no member holds an eta
  * array) and keeps the fastest; *chosen = {rows_per_wave, waves_per_group}
  * as wave_batch_set_kernel takes them. */
 int wave_batch_tune(wave_batch *b, int32_t trial_steps, int32_t chosen[2]);

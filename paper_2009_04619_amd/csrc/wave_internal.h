@@ -130,6 +130,31 @@ struct BatchState {
   int32_t trace_row;     // next trace row
 };
 
+// Blocks of one member in a block-kernel launch: tiles_x x tiles_y tiles, z cut
+// like the streaming kernel's chunks (at the layer faces, so whether a lane is
+// a layer point is fixed for a block).  m*: 2^32 / divisor rounded up, so that
+// mulhi divides (exact for dividend * divisor < 2^32, checked by the launcher).
+struct BlockGrid {
+  int32_t tiles_x, tiles_y;
+  int32_t slab;      // tile rows per XCD and layer of blocks
+  int32_t per_xcd;   // blocks per XCD, slab padding included
+  uint32_t mx, mslab;
+};
+
+// One step of several members in one block-kernel launch, passed by value.
+constexpr int kBlockMembers = 16;
+struct BlockBatch {
+  int32_t n;
+  int32_t back;                  // walk the launch's blocks backwards
+  int32_t begin[kBlockMembers + 1];  // first workgroup of each member (multiples of 8)
+  struct Member {
+    BlockGrid g;
+    int32_t cur;                 // index of u^n in BatchShot::u
+    int32_t step;                // time level n
+    StepIO io;
+  } m[kBlockMembers];
+};
+
 struct EnergyArgs {
   const void* cur;      // u^n
   const void* prev;     // u^{n-1}
@@ -197,6 +222,15 @@ hipError_t launch_sweep_batch_pair(const BatchShot* shots, BatchState* state, in
 // operands of a block requested at once; 4 x 4, and 8 x 8 with damping off and
 // no stochastic rounding.
 bool block_config_supported(int ty, int zc, const SweepArgs& a, int storage);
+// The same for several members of a batch, 4 x 4 blocks.  block_batch_grid sizes
+// a member's share of a launch (workgroups; a multiple of 8).  All members of a
+// launch share lm: 0 damping off, 1 eta array, 2 tables.  launch_record_members
+// samples the receivers of the members' u^n.
+int block_batch_grid(const SweepArgs& a, int nrec, BlockGrid* g);
+hipError_t launch_sweep_block_batch(const BatchShot* shots, const BlockBatch& bb, int storage,
+                                    int lm, hipStream_t s);
+hipError_t launch_record_members(const BatchShot* shots, const BlockBatch& bb, int storage,
+                                 hipStream_t s);
 // Bytes of the state a sweep touches.
 int64_t sweep_footprint(int nx, int ny, int nz, int w, bool damping, bool eta_array, int es);
 // The block a grid's default launch uses; 0, 0 where the streaming kernels

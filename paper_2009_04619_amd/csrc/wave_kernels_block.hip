@@ -243,6 +243,7 @@ __device__ __forceinline__ void block_rows(const SweepArgs& a, const StepIO& io,
       ev[k] = S::enc(res[k]);
   }
   if (smask) {
+#pragma unroll
     for (int s = 0; s < kStepSrc; ++s) {
       if (!(smask >> s & 1)) continue;
 #pragma unroll
@@ -261,38 +262,22 @@ __device__ __forceinline__ void block_rows(const SweepArgs& a, const StepIO& io,
   }
 }
 
-// Blocks of a launch: tiles_x x tiles_y tiles, z cut like the streaming
-// kernel's chunks (at the layer faces, so whether a lane is a layer point is
-// fixed for a block).  m*: 2^32 / divisor rounded up, so that mulhi divides
-// (exact for dividend * divisor < 2^32, checked by the launcher).
-struct BlockGrid {
-  int tiles_x, tiles_y, layers;  // layers of blocks along z
-  int slab;                      // tile rows per XCD and layer
-  int per_xcd;                   // blocks per XCD, slab padding included
-  uint32_t mx, mslab;
-};
 __device__ __forceinline__ int div_by(int n, int d, uint32_t m) {
   return d == 1 ? n : (int)__umulhi((uint32_t)n, m);
 }
 
-// LM: the layer's update, 0 damping off, 1 eta array, 2 tables.
+// Block `at` of XCD xcd.  LM: the layer's update, 0 damping off, 1 eta array,
+// 2 tables.
 template <class S, int TY, int ZC, int LM, bool NTP>
-__global__ __launch_bounds__(64 * TY, 4) void k_sweep_block(SweepArgs a, StepIO io, BlockGrid g) {
-  __shared__ BlockLds<TY, ZC> sm;
-  const int slot = blockIdx.x >> 3;
-  if (slot >= g.per_xcd) {  // receivers of u^n, the last step's field
-    record_row<S>(a, io, (blockIdx.x - 8 * g.per_xcd) * 64 * TY + threadIdx.x);
-    return;
-  }
-  // XCD b mod 8 takes one slab of tile rows through all layers of blocks, so
+__device__ __forceinline__ void block_sweep(const SweepArgs& a, const StepIO& io,
+                                            BlockLds<TY, ZC>& sm, const BlockGrid& g, int xcd,
+                                            int at) {
+  // An XCD takes one slab of tile rows through all layers of blocks, so
   // neighbouring blocks read their halos from one L2 (8 % faster at 256^3
-  // than a contiguous run of layers per XCD).  Odd steps walk the blocks
-  // backwards: what a step touched last is still in the memory-side cache
-  // when the next one starts (256^3: 60.7 -> 51.6 us).
-  const int at = (a.step & 1) ? g.per_xcd - 1 - slot : slot;
+  // than a contiguous run of layers per XCD).
   const int t2 = div_by(at, g.tiles_x, g.mx);
   const int zl = div_by(t2, g.slab, g.mslab);
-  const int ty = (int)(blockIdx.x & 7) * g.slab + t2 - zl * g.slab;
+  const int ty = xcd * g.slab + t2 - zl * g.slab;
   if (ty >= g.tiles_y) return;
   constexpr bool damp = LM != 0;
   const ChunkInfo c = chunk_of(zl, a.nz, a.w, ZC, damp);
@@ -319,20 +304,71 @@ __global__ __launch_bounds__(64 * TY, 4) void k_sweep_block(SweepArgs a, StepIO 
 }
 
 template <class S, int TY, int ZC, int LM, bool NTP>
+__global__ __launch_bounds__(64 * TY, 4) void k_sweep_block(SweepArgs a, StepIO io, BlockGrid g) {
+  __shared__ BlockLds<TY, ZC> sm;
+  const int slot = blockIdx.x >> 3;
+  if (slot >= g.per_xcd) {  // receivers of u^n, the last step's field
+    record_row<S>(a, io, (blockIdx.x - 8 * g.per_xcd) * 64 * TY + threadIdx.x);
+    return;
+  }
+  // Odd steps walk the blocks backwards: what a step touched last is still in
+  // the memory-side cache when the next one starts (256^3: 60.7 -> 51.6 us).
+  block_sweep<S, TY, ZC, LM, NTP>(a, io, sm, g, blockIdx.x & 7,
+                                  (a.step & 1) ? g.per_xcd - 1 - slot : slot);
+}
+
+// Several members of a batch in one launch.  The sweep's arguments come from
+// the batch's table, everything that changes from step to step by value.
+template <class S, int LM>
+__global__ __launch_bounds__(256, 4) void k_sweep_block_batch(const BatchShot* __restrict__ shots,
+                                                              BlockBatch bb) {
+  __shared__ BlockLds<4, 4> sm;
+  const int bid = (int)order_block(blockIdx.x, gridDim.x, bb.back);
+  int m = 0;
+  for (int i = 1; i < bb.n; ++i)
+    if (bid >= bb.begin[i]) m = i;
+  const BlockBatch::Member& e = bb.m[m];
+  SweepArgs a = shots[m].sa;
+  a.cur = shots[m].u[e.cur];
+  a.nxt = shots[m].u[e.cur ^ 1];
+  a.step = e.step;
+  const int local = bid - bb.begin[m];
+  if ((local >> 3) >= e.g.per_xcd) {
+    record_row<S>(a, e.io, (local - 8 * e.g.per_xcd) * 256 + threadIdx.x);
+    return;
+  }
+  block_sweep<S, 4, 4, LM, false>(a, e.io, sm, e.g, local & 7, local >> 3);
+}
+
+template <class S>
+__global__ __launch_bounds__(256) void k_record_members(const BatchShot* __restrict__ shots,
+                                                        BlockBatch bb) {
+  const BlockBatch::Member& e = bb.m[blockIdx.y];
+  SweepArgs a = shots[blockIdx.y].sa;
+  a.cur = shots[blockIdx.y].u[e.cur];
+  record_row<S>(a, e.io, blockIdx.x * 256 + threadIdx.x);
+}
+
+// false: the grid does not fit the index arithmetic.
+bool block_grid(const SweepArgs& a, int ty, int zc, BlockGrid* g) {
+  g->tiles_x = cdiv(a.nx, kTX);
+  g->tiles_y = cdiv(a.ny, ty);
+  g->slab = cdiv(g->tiles_y, 8);
+  const int64_t n = (int64_t)g->tiles_x * g->slab * chunk_count(a.nz, a.w, zc, a.damping != 0);
+  if ((int64_t)(zc + 2 * kR) * a.plane * 4 > kWindowMax ||
+      n * std::max(g->tiles_x, g->slab) >= (int64_t(1) << 32) || n > 0x07ffffff)
+    return false;
+  g->per_xcd = (int)n;
+  auto magic = [](int d) { return (uint32_t)(0xffffffffu / (uint32_t)d + 1u); };
+  g->mx = magic(g->tiles_x);
+  g->mslab = magic(g->slab);
+  return true;
+}
+
+template <class S, int TY, int ZC, int LM, bool NTP>
 hipError_t block_t(const SweepArgs& a, const StepIO& io, hipStream_t st) {
   BlockGrid g;
-  g.tiles_x = cdiv(a.nx, kTX);
-  g.tiles_y = cdiv(a.ny, TY);
-  g.layers = chunk_count(a.nz, a.w, ZC, a.damping != 0);
-  g.slab = cdiv(g.tiles_y, 8);
-  const int64_t n = (int64_t)g.tiles_x * g.slab * g.layers;
-  if ((int64_t)(ZC + 2 * kR) * a.plane * 4 > kWindowMax ||
-      n * std::max(g.tiles_x, g.slab) >= (int64_t(1) << 32) || n > 0x0fffffff)
-    return hipErrorInvalidValue;
-  g.per_xcd = (int)n;
-  auto magic = [](int d) { return (uint32_t)(0xffffffffu / (uint32_t)d + 1u); };
-  g.mx = magic(g.tiles_x);
-  g.mslab = magic(g.slab);
+  if (!block_grid(a, TY, ZC, &g)) return hipErrorInvalidValue;
   const int rec = io.nrec > 0 ? cdiv(io.nrec, 64 * TY) : 0;
   const dim3 grid((unsigned)(8 * g.per_xcd + rec)), blk(64 * TY);
   hipLaunchKernelGGL((k_sweep_block<S, TY, ZC, LM, NTP>), grid, blk, 0, st, a, io, g);
@@ -356,11 +392,8 @@ hipError_t block_s(const SweepArgs& a, const StepIO& io, int ty, int zc, bool nt
 
 bool block_config_supported(int ty, int zc, const SweepArgs& a, int storage) {
   const bool cfg = (ty == 4 && zc == 4) || (ty == 8 && zc == 8 && !a.damping && storage != 3);
-  const int64_t n = (int64_t)cdiv(a.nx, kTX) * cdiv(cdiv(a.ny, ty > 0 ? ty : 1), 8) *
-                    chunk_count(a.nz, a.w, zc > 0 ? zc : 1, a.damping != 0);
-  const int64_t d = std::max(cdiv(a.nx, kTX), cdiv(cdiv(a.ny, ty > 0 ? ty : 1), 8));
-  return cfg && (int64_t)(zc + 2 * kR) * a.plane * 4 <= kWindowMax && n * d < (int64_t(1) << 32) &&
-         n <= 0x0fffffff;
+  BlockGrid g;
+  return cfg && block_grid(a, ty, zc, &g);
 }
 
 int64_t sweep_footprint(int nx, int ny, int nz, int w, bool damping, bool eta_array, int es) {
@@ -396,6 +429,51 @@ hipError_t launch_sweep_block(const SweepArgs& a, const StepIO& io, int storage,
     case 3: return block_s<StBF16SR>(a, io, ty, zc, nt, s);
   }
   return hipErrorInvalidValue;
+}
+
+int block_batch_grid(const SweepArgs& a, int nrec, BlockGrid* g) {
+  if (!block_grid(a, 4, 4, g)) return 0;
+  return 8 * (g->per_xcd + cdiv(cdiv(nrec, 256), 8));
+}
+
+template <class S>
+hipError_t block_batch_s(const BatchShot* shots, const BlockBatch& bb, int lm, hipStream_t st) {
+  const dim3 grid((unsigned)bb.begin[bb.n]);
+  if (lm == 0)
+    hipLaunchKernelGGL((k_sweep_block_batch<S, 0>), grid, dim3(256), 0, st, shots, bb);
+  else if (lm == 1)
+    hipLaunchKernelGGL((k_sweep_block_batch<S, 1>), grid, dim3(256), 0, st, shots, bb);
+  else
+    hipLaunchKernelGGL((k_sweep_block_batch<S, 2>), grid, dim3(256), 0, st, shots, bb);
+  return hipGetLastError();
+}
+
+hipError_t launch_sweep_block_batch(const BatchShot* shots, const BlockBatch& bb, int storage,
+                                    int lm, hipStream_t s) {
+  if (bb.n < 1 || bb.n > kBlockMembers || bb.begin[bb.n] < 1) return hipErrorInvalidValue;
+  switch (storage) {
+    case 0: return block_batch_s<StF32>(shots, bb, lm, s);
+    case 1: return block_batch_s<StBF16>(shots, bb, lm, s);
+    case 2: return block_batch_s<StF16>(shots, bb, lm, s);
+    case 3: return block_batch_s<StBF16SR>(shots, bb, lm, s);
+  }
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_record_members(const BatchShot* shots, const BlockBatch& bb, int storage,
+                                 hipStream_t s) {
+  int most = 0;
+  for (int i = 0; i < bb.n; ++i) most = std::max(most, bb.m[i].io.nrec);
+  if (most == 0) return hipSuccess;
+  const dim3 grid((unsigned)cdiv(most, 256), (unsigned)bb.n);
+  switch (storage) {
+    case 0: hipLaunchKernelGGL(k_record_members<StF32>, grid, dim3(256), 0, s, shots, bb); break;
+    case 1:
+    case 3: hipLaunchKernelGGL(k_record_members<StBF16>, grid, dim3(256), 0, s, shots, bb); break;
+    case 2: hipLaunchKernelGGL(k_record_members<StF16>, grid, dim3(256), 0, s, shots, bb); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
 }
 
 }  // namespace wave

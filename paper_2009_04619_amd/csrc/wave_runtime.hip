@@ -458,6 +458,35 @@ wave::InjectArgs inject_args(const wave_ctx* c) {
   return ia;
 }
 
+// Sources and receivers that a sweep launch takes along: the sources' places
+// (at most kStepSrc; unused entries match no point), their samples of step n,
+// and the receivers of u^n, trace row `row`, if there is one to sample.
+wave::StepIO step_sources(const wave_ctx* c) {
+  wave::StepIO io;
+  memset(&io, 0, sizeof(io));
+  io.nsrc = c->nsrc;
+  for (int s = 0; s < wave::kStepSrc; ++s) {
+    io.sz[s] = -1;
+    if (s >= c->nsrc) continue;
+    io.sx[s] = c->src_host[3 * s];
+    io.sy[s] = c->src_host[3 * s + 1];
+    io.sz[s] = c->src_host[3 * s + 2];
+  }
+  return io;
+}
+
+void step_samples(const wave_ctx* c, int64_t n, wave::StepIO* io) {
+  const int wrow = std::max(c->d.max_steps, 1);
+  for (int s = 0; s < io->nsrc; ++s)
+    io->sw[s] = n < wrow ? c->wav_host[(size_t)s * wrow + n] : 0.0f;
+}
+
+void step_receivers(const wave_ctx* c, bool sample, int row, wave::StepIO* io) {
+  io->nrec = sample ? c->nrec : 0;
+  io->rec_off = reinterpret_cast<const int64_t*>(c->at(c->plan.rec_off));
+  io->row = io->nrec > 0 ? reinterpret_cast<double*>(c->at(c->plan.traces)) + (int64_t)row * c->nrec : nullptr;
+}
+
 int64_t offset_of(const wave_ctx* c, int i, int j, int k) {
   return (int64_t)k * c->L.plane + (int64_t)j * c->L.pitch + i;
 }
@@ -487,15 +516,32 @@ struct wave_batch {
   std::vector<wave::BatchShot> h_shots;
   std::vector<wave::BatchState> h_state;
   int ry, nw;
-  bool eta_any;               // some member holds a per-point eta array
-  int64_t total_blocks;
+  bool by_size;               // no tile set: each member's sweep is chosen by its size
+  struct Group;
+  std::vector<Group> groups;  // the members in launch order (batch_layout)
   bool layout_dirty;          // membership or tile shape changed
   int graph_steps;            // steps per captured graph (0 = plain launches)
-  // captured step blocks, one per number of active members K (the active
-  // members are the first K: runs order members by steps left)
-  std::vector<std::pair<int, hipGraphExec_t>> graphs;
-  std::vector<int64_t> prefix_blocks;  // workgroups of the first k members
+  // captured step blocks, one per group and number of its active members K
+  // (the active members are its first K: runs order members by steps left)
+  struct Graph {
+    int group, k;
+    hipGraphExec_t exec;
+  };
+  std::vector<Graph> graphs;
   bool broken;
+};
+
+// Members first .. first + count - 1 of a batch take all their steps of a run
+// together, one launch (and one for sources and receivers, unless `block`) per
+// step, before the next group starts.
+struct wave_batch::Group {
+  int first, count;
+  bool block;                 // the block kernel (lm: 0 damping off, 1 eta array, 2 tables)
+  int lm;
+  int ry, nw;                 // otherwise the streaming tile (ry 0: two points per lane)
+  bool eta_any;               // some member holds a per-point eta array
+  std::vector<int64_t> prefix;        // workgroups of the first k members
+  std::vector<wave::BlockGrid> grid;  // block: each member's blocks
 };
 
 namespace {
@@ -582,72 +628,211 @@ int pair_zchunk(const wave_ctx* c, int ty, int zchunk, int semi_nw = 0) {
   return std::min(zc, lim);
 }
 
+// State of a member that its sweep touches, and what a group of several members
+// may hold to stay in the 256 MB memory-side cache between steps (8 float32
+// shots of 128-256 cells, 46-145 MB each, us per step at 100, 150, 200, 240,
+// 280 MB: 233, 233, 224, 242, 236).
+constexpr int64_t kGroupBytes = 200 * 1000000LL;
+int64_t member_bytes(const wave_ctx* c) {
+  return wave::sweep_footprint(c->L.nx, c->L.ny, c->L.nz, c->d.w, c->damp, eta_array(&c->d), c->es);
+}
+
 void batch_drop_graphs(wave_batch* b) {
-  for (auto& g : b->graphs) (void)hipGraphExecDestroy(g.second);
+  for (auto& g : b->graphs) (void)hipGraphExecDestroy(g.exec);
   b->graphs.clear();
 }
 
-// Rebuild the member tables (static part); targets are filled per run.
+// Whether a member of a batch without a set tile runs the block kernel: its
+// own default launch does, and its sources fit one launch.
+bool batch_block_member(const wave_ctx* c) {
+  int ty, zc;
+  const wave::SweepArgs a = sweep_args(c);
+  wave::block_default(a, kernel_storage(&c->d), &ty, &zc);
+  wave::BlockGrid g;
+  return ty > 0 && c->nsrc <= wave::kStepSrc && member_bytes(c) <= 280 * 1000000LL &&
+         wave::block_batch_grid(a, c->nrec, &g) > 0;
+}
+
+// Launch order of a member in a batch without a set tile: members of one kind
+// can share a launch.
+int batch_kind(const wave_ctx* c) {
+  const int lm = !c->damp ? 0 : eta_array(&c->d) ? 1 : 2;
+  return batch_block_member(c) ? lm : 3 + (lm == 1 ? 1 : 0);
+}
+
+// Rebuild the member tables (static part) and the groups; targets are filled
+// per run.  With a set tile all members form one group.  Without one, those
+// that run the block kernel are grouped, in order, while their states together
+// fit the memory-side cache: a group's steps then read what its last step left
+// there, where one launch per step over all members streams every state from
+// memory each time (8 float32 shots of 128-256 cells, 765 MB: 279 us per step
+// in 64 x 8 tiles together, 224 in groups).  Streaming members go around that
+// cache and stay together (two bf16 shots of 352 cells 199 us, 215 one by one).
 void batch_layout(wave_batch* b) {
   b->h_shots.resize(b->members.size());
-  b->prefix_blocks.assign(1, 0);
-  int64_t begin = 0;
-  // rows_per_wave 0: two points per lane, 128 x nw tiles
-  const bool pair = b->ry == 0;
-  const int ty = pair ? b->nw : b->ry * b->nw;
+  b->groups.clear();
+  int64_t bytes = 0;
   for (size_t i = 0; i < b->members.size(); ++i) {
     wave_ctx* c = b->members[i];
+    const int kind = b->by_size ? batch_kind(c) : 0;
+    const bool block = b->by_size && kind < 3;
+    const int64_t mine = member_bytes(c);
+    const bool fits = !b->groups.empty() &&
+                      (!b->by_size || (kind == batch_kind(b->members[i - 1]) &&
+                                       (!block || (bytes + mine <= kGroupBytes &&
+                                                   b->groups.back().count < wave::kBlockMembers))));
+    if (!fits) {
+      wave_batch::Group g;
+      g.first = (int)i;
+      g.count = 0;
+      g.block = block;
+      g.lm = kind;
+      g.ry = b->ry;
+      g.nw = b->nw;
+      if (b->by_size) {
+        g.ry = c->es == 2 && b->kstore != 3 && pair_zchunk(c, 8, 0) >= 1 ? 0 : 1;
+        g.nw = 8;
+      }
+      g.eta_any = false;
+      g.prefix.assign(1, 0);
+      b->groups.push_back(g);
+      bytes = 0;
+    }
+    bytes += mine;
+    wave_batch::Group& g = b->groups.back();
+    g.count += 1;
+    g.eta_any = g.eta_any || eta_array(&c->d);
     wave::BatchShot& e = b->h_shots[i];
     memset(&e, 0, sizeof(e));
     e.sa = sweep_args(c);
     e.u[0] = c->u_origin(std::min(c->icur, c->iprev));
     e.u[1] = c->u_origin(std::max(c->icur, c->iprev));
-    e.tiles_x = (c->L.nx + (pair ? 2 : 1) * wave::kTX - 1) / ((pair ? 2 : 1) * wave::kTX);
-    e.tiles_y = (c->L.ny + ty - 1) / ty;
-    e.zchunk = pair ? pair_zchunk(c, b->nw, c->zchunk) : stream_zchunk(c, b->ry, b->nw, c->zchunk);
-    const int chunks = wave::stream_chunk_count(c->L.nz, c->d.w, e.zchunk, c->damp);
-    e.block_begin = begin;
-    // tile rows padded to 8 slabs: a multiple of 8 blocks per member
-    begin += (int64_t)e.tiles_x * 8 * ((e.tiles_y + 7) / 8) * chunks;
-    b->prefix_blocks.push_back(begin);
+    e.block_begin = g.prefix.back();
     e.target = 0;
     e.inj = inject_args(c);
+    if (g.block) {
+      wave::BlockGrid bg;
+      g.prefix.push_back(g.prefix.back() + wave::block_batch_grid(e.sa, c->nrec, &bg));
+      g.grid.push_back(bg);
+      continue;
+    }
+    // rows_per_wave 0: two points per lane, 128 x nw tiles
+    const bool pair = g.ry == 0;
+    const int ty = pair ? g.nw : g.ry * g.nw;
+    e.tiles_x = (c->L.nx + (pair ? 2 : 1) * wave::kTX - 1) / ((pair ? 2 : 1) * wave::kTX);
+    e.tiles_y = (c->L.ny + ty - 1) / ty;
+    e.zchunk = pair ? pair_zchunk(c, g.nw, c->zchunk) : stream_zchunk(c, g.ry, g.nw, c->zchunk);
+    const int chunks = wave::stream_chunk_count(c->L.nz, c->d.w, e.zchunk, c->damp);
+    // tile rows padded to 8 slabs: a multiple of 8 blocks per member
+    g.prefix.push_back(g.prefix.back() + (int64_t)e.tiles_x * 8 * ((e.tiles_y + 7) / 8) * chunks);
   }
-  b->total_blocks = begin;
-  b->eta_any = false;
-  for (wave_ctx* c : b->members) b->eta_any = b->eta_any || eta_array(&c->d);
   b->layout_dirty = false;
   batch_drop_graphs(b);
 }
 
-// One step of the first k members (those still taking steps in this run).
-hipError_t batch_launch_step(wave_batch* b, int k) {
-  hipError_t e = b->ry == 0
-                     ? wave::launch_sweep_batch_pair(b->d_shots, b->d_state, k, b->prefix_blocks[k],
-                                                     b->kstore, b->nw, b->stream)
-                     : wave::launch_sweep_batch(b->d_shots, b->d_state, k, b->prefix_blocks[k],
-                                                b->kstore, b->ry, b->nw, b->eta_any, b->stream);
+// One step of the first k members of a streaming group (those still taking
+// steps in this run).
+hipError_t batch_launch_step(wave_batch* b, const wave_batch::Group& g, int k) {
+  wave::BatchShot* shots = b->d_shots + g.first;
+  wave::BatchState* state = b->d_state + g.first;
+  hipError_t e = g.ry == 0 ? wave::launch_sweep_batch_pair(shots, state, k, g.prefix[k], b->kstore,
+                                                           g.nw, b->stream)
+                           : wave::launch_sweep_batch(shots, state, k, g.prefix[k], b->kstore, g.ry,
+                                                      g.nw, g.eta_any, b->stream);
   if (e != hipSuccess) return e;
-  return wave::launch_inject_batch(b->d_shots, b->d_state, k, b->kstore, b->stream);
+  return wave::launch_inject_batch(shots, state, k, b->kstore, b->stream);
 }
 
-// The captured block of graph_steps steps for the first k members.
-hipError_t batch_graph(wave_batch* b, int k, hipGraphExec_t* out) {
+// The captured block of graph_steps steps for the first k members of a group.
+hipError_t batch_graph(wave_batch* b, int group, int k, hipGraphExec_t* out) {
   for (auto& g : b->graphs)
-    if (g.first == k) {
-      *out = g.second;
+    if (g.group == group && g.k == k) {
+      *out = g.exec;
       return hipSuccess;
     }
   hipGraph_t g = nullptr;
   hipError_t e = hipStreamBeginCapture(b->stream, hipStreamCaptureModeRelaxed);
   if (e != hipSuccess) return e;
-  for (int t = 0; t < b->graph_steps && e == hipSuccess; ++t) e = batch_launch_step(b, k);
+  for (int t = 0; t < b->graph_steps && e == hipSuccess; ++t)
+    e = batch_launch_step(b, b->groups[group], k);
   hipError_t e2 = hipStreamEndCapture(b->stream, &g);
   if (e == hipSuccess) e = e2;
   if (e == hipSuccess) e = hipGraphInstantiate(out, g, nullptr, nullptr, 0);
   if (g) (void)hipGraphDestroy(g);
-  if (e == hipSuccess) b->graphs.emplace_back(k, *out);
+  if (e == hipSuccess) b->graphs.push_back({group, k, *out});
   return e;
+}
+
+// All steps of a streaming group: segments of constant active count k, steps
+// [j, t_{k-1}) running its first k members; whole captured blocks where a
+// segment is long enough.
+hipError_t batch_run_stream(wave_batch* b, int group) {
+  const wave_batch::Group& g = b->groups[group];
+  const wave::BatchShot* h = b->h_shots.data() + g.first;
+  int k = g.count;
+  for (int32_t j = 0; j < h[0].target;) {
+    while (h[k - 1].target <= j) --k;
+    const int32_t seg_end = h[k - 1].target;
+    int32_t left = seg_end - j;
+    if (b->graph_steps > 0 && left >= b->graph_steps) {
+      hipGraphExec_t ge = nullptr;
+      hipError_t e = batch_graph(b, group, k, &ge);
+      for (; e == hipSuccess && left >= b->graph_steps; left -= b->graph_steps)
+        e = hipGraphLaunch(ge, b->stream);
+      if (e != hipSuccess) return e;
+    }
+    for (; left > 0; --left) {
+      const hipError_t e = batch_launch_step(b, g, k);
+      if (e != hipSuccess) return e;
+    }
+    j = seg_end;
+  }
+  return hipSuccess;
+}
+
+// All steps of a block group, one launch each (what changes from step to step
+// travels in the launch's arguments, so these are never captured), and one for
+// the receivers of every member's last step.
+hipError_t batch_run_block(wave_batch* b, const wave_batch::Group& g) {
+  const wave::BatchShot* h = b->h_shots.data() + g.first;
+  wave::BlockBatch bb;
+  memset(&bb, 0, sizeof(bb));
+  for (int i = 0; i < g.count; ++i) {
+    const wave_ctx* c = b->members[g.first + i];
+    bb.m[i].g = g.grid[i];
+    bb.m[i].io = step_sources(c);
+    bb.begin[i] = (int32_t)g.prefix[i];
+  }
+  auto at_step = [&](int i, int32_t t) {   // member i before its step t of this run
+    const wave_ctx* c = b->members[g.first + i];
+    wave::BlockBatch::Member& m = bb.m[i];
+    m.cur = (c->icur < c->iprev ? 0 : 1) ^ (t & 1);
+    m.step = (int32_t)c->step + t;
+    step_samples(c, c->step + t, &m.io);
+    step_receivers(c, t > 0, c->trace_count + t - 1, &m.io);
+  };
+  int k = g.count;
+  for (int32_t t = 0; t < h[0].target; ++t) {
+    while (h[k - 1].target <= t) --k;
+    for (int i = 0; i < k; ++i) at_step(i, t);
+    bb.n = k;
+    bb.back = t & 1;
+    bb.begin[k] = (int32_t)g.prefix[k];
+    hipError_t e;
+    if (k == 1) {   // as on its own: no table to look up (2.5 us less)
+      wave::SweepArgs a = h[0].sa;
+      a.cur = h[0].u[bb.m[0].cur];
+      a.nxt = h[0].u[bb.m[0].cur ^ 1];
+      a.step = bb.m[0].step;
+      e = wave::launch_sweep_block(a, bb.m[0].io, b->kstore, 4, 4, b->stream);
+    } else {
+      e = wave::launch_sweep_block_batch(b->d_shots + g.first, bb, b->kstore, g.lm, b->stream);
+    }
+    if (e != hipSuccess) return e;
+  }
+  for (int i = 0; i < g.count; ++i) at_step(i, h[i].target);
+  bb.n = g.count;
+  return wave::launch_record_members(b->d_shots + g.first, bb, b->kstore, b->stream);
 }
 
 }  // namespace
@@ -1064,8 +1249,12 @@ int wave_step(wave_ctx* c, int32_t n) {
   // the step before in its own launch; the last step's receivers follow it
   const bool fused = c->variant == WAVE_KERNEL_BLOCK && c->nsrc <= wave::kStepSrc;
   wave::StepIO io;
-  memset(&io, 0, sizeof(io));
-  for (int s = 0; s < wave::kStepSrc; ++s) io.sz[s] = -1;  // unused entries match no point
+  if (fused) {
+    io = step_sources(c);
+  } else {
+    memset(&io, 0, sizeof(io));
+    for (int& z : io.sz) z = -1;
+  }
   auto launch_one = [&](const wave::SweepArgs& s) -> hipError_t {
     if (c->variant == WAVE_KERNEL_BLOCK)
       return wave::launch_sweep_block(s, io, kernel_storage(&c->d), c->shp[1], c->shp[2], c->stream);
@@ -1090,25 +1279,13 @@ int wave_step(wave_ctx* c, int32_t n) {
   wave::InjectArgs ia = inject_args(c);
 
   double* const traces = c->nrec > 0 ? reinterpret_cast<double*>(c->at(c->plan.traces)) : nullptr;
-  const int wrow = std::max(c->d.max_steps, 1);
-  if (fused) {
-    io.nsrc = c->nsrc;
-    for (int s = 0; s < c->nsrc; ++s) {
-      io.sx[s] = c->src_host[3 * s];
-      io.sy[s] = c->src_host[3 * s + 1];
-      io.sz[s] = c->src_host[3 * s + 2];
-    }
-    io.rec_off = ia.rec_off;
-  }
   for (int t = 0; t < n; ++t) {
     sa.cur = c->u_origin(c->icur);
     sa.nxt = c->u_origin(c->iprev);
     sa.step = (int32_t)c->step;
     if (fused) {
-      for (int s = 0; s < c->nsrc; ++s)
-        io.sw[s] = c->step < wrow ? c->wav_host[(size_t)s * wrow + c->step] : 0.0f;
-      io.nrec = t > 0 ? c->nrec : 0;
-      if (t > 0 && traces) io.row = traces + (int64_t)(c->trace_count - 1) * c->nrec;
+      step_samples(c, c->step, &io);
+      step_receivers(c, t > 0, c->trace_count - 1, &io);
     }
     hipEvent_t e1;
     int rc = timing_begin(c, &e1);
@@ -1643,8 +1820,7 @@ int wave_batch_create(int32_t storage, int32_t max_shots, void* dev_arena, size_
   b->d_state = reinterpret_cast<wave::BatchState*>(b->arena + soff);
   b->ry = 1;
   b->nw = 16;
-  b->eta_any = false;
-  b->total_blocks = 0;
+  b->by_size = true;
   b->layout_dirty = true;
   b->graph_steps = 0;
   b->broken = false;
@@ -1681,9 +1857,9 @@ int wave_batch_add(wave_batch* b, wave_ctx* c, int32_t nsteps) {
   if (c->step + nsteps > 0x7fffffff) return fail(WAVE_EINVAL, "step counter overflow");
   if (wave::stream_zchunk_limit(c->L.plane) < 1)
     return fail(WAVE_EINVAL, "z planes too large for the batched streaming kernel");
-  if (b->ry == 0 && eta_array(&c->d))
+  if (!b->by_size && b->ry == 0 && eta_array(&c->d))
     return fail(WAVE_EINVAL, "the batch runs the two-points-per-lane kernel, which takes no eta array");
-  if (b->ry > 0 && !wave::stream_config_supported(b->ry, b->nw, eta_array(&c->d)))
+  if (!b->by_size && b->ry > 0 && !wave::stream_config_supported(b->ry, b->nw, eta_array(&c->d)))
     return fail(WAVE_EINVAL, "the batch's tile is not compiled for a member with an eta array");
   // the batch's launches come after everything queued so far on the member's stream
   JOIN_CTX(c);
@@ -1733,7 +1909,11 @@ int wave_batch_remaining(const wave_batch* b, const wave_ctx* c, int32_t* remain
 
 int wave_batch_set_kernel(wave_batch* b, int32_t ry, int32_t nw) {
   CHECK_BATCH(b);
-  if (ry == 0) {   // two points per lane
+  const bool by_size = ry == 4 && nw == 4;
+  if (by_size) {
+    ry = 1;
+    nw = 16;
+  } else if (ry == 0) {   // two points per lane
     if (nw != 8 && nw != 16) return fail(WAVE_EINVAL, "two points per lane: 8 or 16 rows");
     for (wave_ctx* c : b->members)
       if (eta_array(&c->d)) return fail(WAVE_EINVAL, "a member holds an eta array (two points per lane takes none)");
@@ -1745,6 +1925,7 @@ int wave_batch_set_kernel(wave_batch* b, int32_t ry, int32_t nw) {
   }
   b->ry = ry;
   b->nw = nw;
+  b->by_size = by_size;
   b->layout_dirty = true;
   return WAVE_OK;
 }
@@ -1764,13 +1945,17 @@ int wave_batch_run(wave_batch* b, int32_t n) {
     if (c->broken) return fail(WAVE_ESTATE, "a member context is broken");
   const size_t nm = b->members.size();
   if (nm == 0 || n == 0) return WAVE_OK;
-  // members ordered by the steps they take in this run, most first: at every
-  // step the members still running are a prefix, and only their workgroups
-  // are launched
+  // members ordered by kind (without a set tile) and then by the steps they
+  // take in this run, most first: at every step the members of a group still
+  // running are a prefix, and only their workgroups are launched
   {
     std::vector<size_t> order(nm);
     for (size_t i = 0; i < nm; ++i) order[i] = i;
+    std::vector<int> kind(nm, 0);
+    if (b->by_size)
+      for (size_t i = 0; i < nm; ++i) kind[i] = batch_kind(b->members[i]);
     std::stable_sort(order.begin(), order.end(), [&](size_t x, size_t y) {
+      if (kind[x] != kind[y]) return kind[x] < kind[y];
       return std::min(b->remaining[x], n) > std::min(b->remaining[y], n);
     });
     bool moved = false;
@@ -1823,26 +2008,9 @@ int wave_batch_run(wave_batch* b, int32_t n) {
     BCHK(b, hipEventRecord(b->ev_copy[k], b->stream), "hipEventRecord");
     b->runs += 1;
   }
-  // segments of constant active count k: steps [j, t_{k-1}) run the first k
-  // members; whole captured blocks where a segment is long enough
-  int32_t j = 0;
-  size_t k = nm;
-  while (j < steps) {
-    while (k > 0 && b->h_shots[k - 1].target <= j) --k;
-    const int32_t seg_end = b->h_shots[k - 1].target;
-    int32_t left = seg_end - j;
-    if (b->graph_steps > 0 && left >= b->graph_steps) {
-      hipGraphExec_t g = nullptr;
-      hipError_t e = batch_graph(b, (int)k, &g);
-      if (e != hipSuccess) return batch_fail(b, e, "batch graph capture");
-      for (; left >= b->graph_steps; left -= b->graph_steps)
-        BCHK(b, hipGraphLaunch(g, b->stream), "hipGraphLaunch");
-    }
-    for (; left > 0; --left) {
-      hipError_t e = batch_launch_step(b, (int)k);
-      if (e != hipSuccess) return batch_fail(b, e, "batch launch");
-    }
-    j = seg_end;
+  for (size_t gi = 0; gi < b->groups.size(); ++gi) {
+    const hipError_t e = b->groups[gi].block ? batch_run_block(b, b->groups[gi]) : batch_run_stream(b, (int)gi);
+    if (e != hipSuccess) return batch_fail(b, e, "batch launch");
   }
   BCHK(b, hipEventRecord(b->ev_out, b->stream), "hipEventRecord");
   BCHK(b, hipStreamWaitEvent(b->user_stream, b->ev_out, 0), "hipStreamWaitEvent");
@@ -1862,15 +2030,16 @@ int wave_batch_tune(wave_batch* b, int32_t trial_steps, int32_t chosen[2]) {
   CHECK_BATCH(b);
   if (trial_steps < 1) return fail(WAVE_EINVAL, "trial_steps < 1");
   const int nshape = (int)(sizeof(kShapes) / sizeof(kShapes[0]));
-  const int ry0 = b->ry, nw0 = b->nw;
   float best = 0.0f;
-  int pr = ry0, pn = nw0;
-  // the compiled one-point tiles, then two points per lane (128 x 16, 128 x 8)
-  // when no member holds an eta array
+  int pr = 4, pn = 4;
+  // each member by its size (in the place of the 64 x 8 tile of four
+  // wavefronts), the compiled one-point tiles, then two points per lane (128 x
+  // 16, 128 x 8) when no member holds an eta array
   std::vector<std::array<int, 2>> shapes;
   bool pair_ok = true;
   for (wave_ctx* c : b->members) pair_ok = pair_ok && !eta_array(&c->d);
-  for (int k = 0; k < nshape; ++k)
+  shapes.push_back({4, 4});
+  for (int k = 0; k < nshape - 1; ++k)
     if (wave::stream_config_supported(kShapes[k][0], kShapes[k][1], !pair_ok))
       shapes.push_back({kShapes[k][0], kShapes[k][1]});
   if (pair_ok) {
@@ -1878,14 +2047,13 @@ int wave_batch_tune(wave_batch* b, int32_t trial_steps, int32_t chosen[2]) {
     shapes.push_back({0, 8});
   }
   for (const auto& sh : shapes) {
-    b->ry = sh[0];
-    b->nw = sh[1];
-    b->layout_dirty = true;
+    int rc = wave_batch_set_kernel(b, sh[0], sh[1]);
+    if (rc != WAVE_OK) return rc;
     hipEvent_t e0, e1;
     BCHK(b, hipEventCreate(&e0), "hipEventCreate");
     BCHK(b, hipEventCreate(&e1), "hipEventCreate");
     BCHK(b, hipEventRecord(e0, b->user_stream), "hipEventRecord");
-    int rc = wave_batch_run(b, trial_steps);
+    rc = wave_batch_run(b, trial_steps);
     if (rc != WAVE_OK) {
       (void)hipEventDestroy(e0);
       (void)hipEventDestroy(e1);
@@ -1903,9 +2071,8 @@ int wave_batch_tune(wave_batch* b, int32_t trial_steps, int32_t chosen[2]) {
       pn = sh[1];
     }
   }
-  b->ry = pr;
-  b->nw = pn;
-  b->layout_dirty = true;
+  const int rc = wave_batch_set_kernel(b, pr, pn);
+  if (rc != WAVE_OK) return rc;
   if (chosen) {
     chosen[0] = pr;
     chosen[1] = pn;

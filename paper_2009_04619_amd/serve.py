@@ -101,11 +101,10 @@ class GpuExecutor(Executor):
     events).
 
     `tiles` gives each storage type's batch sweep tile as
-    wave_batch_set_kernel takes it; the defaults are what the batch tuner
-    picked for mixed 128-384^3 shots on MI355X (one point per lane, 64 x 8,
-    for float32; two points per lane, 128 x 8, for 16-bit storage)."""
+    wave_batch_set_kernel takes it; the default leaves each request's sweep
+    to its size."""
 
-    TILES = {"f32": (1, 8), "bf16": (0, 8), "f16": (0, 8)}
+    TILES = {"f32": (4, 4), "bf16": (4, 4), "f16": (4, 4)}
 
     def __init__(self, device="cuda:0", graph_steps=0, max_shots=128, tiles=None):
         import torch

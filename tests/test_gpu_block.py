@@ -91,3 +91,59 @@ def test_block_refusals(W):
         assert W.wave_set_kernel(sh.ctx, *bad) == W.WAVE_EINVAL, bad
     assert W.wave_set_kernel(sh.ctx, 10, 1, 4, 4) == W.WAVE_OK
     sh.close()
+
+
+def _solo(W, args, n):
+    sh = _shot(W, *args)
+    sh.set_kernel(W.WAVE_KERNEL_DIRECT)
+    sh.step(n)
+    return _state(W, sh)
+
+
+def _shot(W, nx, ny, nz, w, nsrc, eta, damping):
+    rng = np.random.default_rng(nx + ny + nsrc)
+    vel = rng.uniform(1500.0, 4000.0, (nz, ny, nx)).astype(np.float32)
+    e = rng.uniform(0.0, 0.3, (nz, ny, nx)).astype(np.float32) if eta else None
+    sh = W.Shot(nx, ny, nz, w, 10.0, 10.0, 10.0, 9e-4, vel, eta=e, damping=damping, max_src=8,
+                max_rec=300, max_steps=16)
+    for s in range(nsrc):
+        p = (nx // 2, ny // 2, nz // 2) if s % 3 == 0 else tuple(int(rng.integers(0, n)) for n in (nx, ny, nz))
+        sh.inject(*p, rng.standard_normal(16).astype(np.float32))
+    sh.record(np.stack([rng.integers(0, n, 300) for n in (nx, ny, nz)], axis=1))
+    return sh
+
+
+def _state(W, sh):
+    out = [sh.read(W.WAVE_FIELD_U), sh.read(W.WAVE_FIELD_UPREV), sh.read(W.WAVE_FIELD_PHI), sh.traces()]
+    sh.close()
+    return out
+
+
+# nx, ny, nz, w, sources, eta array, damping
+MIXED = [(70, 45, 37, 5, 2, False, True), (64, 30, 40, 4, 1, True, True), (33, 65, 21, 0, 4, False, False),
+         (48, 40, 36, 6, 6, False, True),      # more sources than a launch takes: the streaming tile
+         (40, 40, 40, 4, 6, True, True), (90, 20, 24, 3, 0, False, True)]
+MANY = [(20 + 3 * i, 24, 18 + i, 3, 1, False, True) for i in range(19)]     # more members than a launch holds
+LARGE = [(224, 200, 208, 20, 1, False, True)] * 2 + [(64, 64, 64, 8, 1, False, True)]   # more than one group
+
+
+@pytest.mark.parametrize("graph", [0, 2])
+@pytest.mark.parametrize("members", [MIXED, MANY, LARGE], ids=["mixed", "many", "large"])
+def test_batch_by_size_equals_solo(W, members, graph):
+    """A batch without a set tile: kinds of sweep side by side, members that
+    stop early, runs that continue, several groups."""
+    say(f"case batch by size, {len(members)} members, graph {graph}")
+    n = [3 + (5 * i) % 7 for i in range(len(members))]
+    b = W.Batch(max_shots=len(members))
+    b.set_graph(graph)
+    shots = [_shot(W, *m) for m in members]
+    for sh, k in zip(shots, n):
+        b.add(sh, k)
+    b.run(4)
+    b.run(16)
+    for sh in shots:
+        assert b.remaining(sh) == 0
+    b.close()
+    for i, sh in enumerate(shots):
+        for x, y in zip(_state(W, sh), _solo(W, members[i], n[i])):
+            assert x.shape == y.shape and np.array_equal(x, y), (i, members[i])
