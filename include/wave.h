@@ -333,10 +333,11 @@ int wave_energy_noalloc(wave_ctx *ctx, double *dev_out);
                                 workgroup, every operand of the block
                                 requested at once, up to 4 sources and the
                                 receivers in the same launch; rows_per_wave =
-                                1, (waves_per_group, zchunk) = (ty, zc) in
-                                {(4,4)}, and (8,8) with damping off and no
-                                stochastic rounding; zc + 8 float planes below
-                                2 GiB (EINVAL)                            */
+                                1, (waves_per_group, zchunk) = (ty, zc): (4,4);
+                                (8,4), two points per lane, with 16-bit storage,
+                                no eta array and no stochastic rounding; (8,8)
+                                with damping off and no stochastic rounding;
+                                zc + 8 float planes below 2 GiB (EINVAL)  */
 
 /* Select the sweep kernel and its tile: rows_per_wave (RY) and
  * waves_per_group (NW) give a 64 x (RY*NW) xy tile; zchunk is the number of
@@ -344,8 +345,8 @@ int wave_energy_noalloc(wave_ctx *ctx, double *dev_out);
  * combinations are accepted (EINVAL otherwise): (RY, NW) in
  * {(1,16), (1,8), (2,8), (2,4)}, and (2,16) (64 x 32 tiles) without an eta
  * array.  The default is WAVE_KERNEL_BLOCK where the state (u^n, u^{n-1}, vp,
- * phi and eta of the points that have them) is at most 280 MB, and with
- * damping off on larger grids too; else, with 16-bit storage and no eta array,
+ * phi and eta of the points that have them) is at most 280 MB (360 MB with two
+ * points per lane), and with damping off on larger grids too; else, with 16-bit storage and no eta array,
  * WAVE_KERNEL_PAIR with 8 rows (with stochastic rounding 16 rows, and only on
  * the large grids of the next clause); else WAVE_KERNEL_PERSIST with (1,16)
  * tiles and its automatic chunk (half the streaming kernel's) on grids large

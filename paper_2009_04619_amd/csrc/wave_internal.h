@@ -136,7 +136,8 @@ struct BatchState {
 // mulhi divides (exact for dividend * divisor < 2^32, checked by the launcher).
 struct BlockGrid {
   int32_t tiles_x, tiles_y;
-  int32_t slab;      // tile rows per XCD and layer of blocks
+  int32_t slab;      // most tile rows of an XCD in a layer of blocks
+  int32_t half;      // first layer of the upper half
   int32_t per_xcd;   // blocks per XCD, slab padding included
   uint32_t mx, mslab;
 };
@@ -219,29 +220,32 @@ hipError_t launch_sweep_pair(const SweepArgs& a, int storage, int ty, int zchunk
 hipError_t launch_sweep_batch_pair(const BatchShot* shots, BatchState* state, int nshots,
                                    int64_t total_blocks, int storage, int ty, hipStream_t s);
 // Sweep of small grids (wave_kernels_block.hip): 64 x ty x zc blocks, all
-// operands of a block requested at once; 4 x 4, and 8 x 8 with damping off and
-// no stochastic rounding.
+// operands of a block requested at once; 4 x 4, 8 x 4 (two points per lane) with
+// 16-bit storage, no eta array and no stochastic rounding, and 8 x 8 with damping
+// off and no stochastic rounding.
 bool block_config_supported(int ty, int zc, const SweepArgs& a, int storage);
-// The same for several members of a batch, 4 x 4 blocks.  block_batch_grid sizes
+// The same for several members of a batch, 4 x 4 blocks, or (duo) 8 x 4.  block_batch_grid sizes
 // a member's share of a launch (workgroups; a multiple of 8).  All members of a
 // launch share lm: 0 damping off, 1 eta array, 2 tables.  launch_record_members
 // samples the receivers of the members' u^n.
-int block_batch_grid(const SweepArgs& a, int nrec, BlockGrid* g);
+int block_batch_grid(const SweepArgs& a, bool duo, int nrec, BlockGrid* g);
 hipError_t launch_sweep_block_batch(const BatchShot* shots, const BlockBatch& bb, int storage,
-                                    int lm, hipStream_t s);
+                                    int lm, bool duo, hipStream_t s);
 hipError_t launch_record_members(const BatchShot* shots, const BlockBatch& bb, int storage,
                                  hipStream_t s);
 // Bytes of the state a sweep touches.
 int64_t sweep_footprint(int nx, int ny, int nz, int w, bool damping, bool eta_array, int es);
 // The block a grid's default launch uses; 0, 0 where the streaming kernels
-// are the faster ones.  With a layer, 4 x 4 up to 280 MB of state, about what
-// the memory-side cache keeps (us per step, block against the best streaming
-// tile: float32 256^3, 228 MB, 52 against 65; 288^3, 325 MB, 89 against 90; 320^3
-// 117 against 113; bf16 288^3, 230 MB, 72 against 79; 320^3, 306 MB, 95 against
-// 93).  Without a layer 8 x 8 blocks on all but small grids (float32 256^3 40
-// against 37 with 4 x 4, 384^3 137 against 151 streaming, 600^3 659 against 685;
-// bf16 128^3, 17 MB, 6.6 against 7.5 with 4 x 4, 256^3 27 against 33, 512^3 220
-// against 221 streaming).
+// are the faster ones.  With a layer, blocks up to about the state the
+// memory-side cache keeps, 280 MB, and 360 MB with two points per lane (us per
+// step, block against the best streaming tile: float32 256^3, 228 MB, 52 against
+// 65; 288^3, 325 MB, 89 against 90; 320^3 117 against 113; bf16 320^3, 306 MB, 84
+// against 95; 384 x 320 x 300, 347 MB, 97 against 105; 352^3, 415 MB, 123 against
+// 117).  16-bit storage takes two points per lane from 10 MB on (bf16 64^3 5.2
+// against 4.5 with one, 128 x 112 x 96 7.2 against 7.9, 256^3 42 against 50, 320^3
+// 84 against 93; without a layer 256^3 27.7 against 36.4).  Without a layer,
+// larger grids take 8 x 8 blocks (float32 256^3 40 against 41 with 4 x 4, 384^3 137
+// against 151 streaming, 600^3 659 against 685; bf16 512^3 220 against 221).
 void block_default(const SweepArgs& a, int storage, int* ty, int* zc);
 hipError_t launch_sweep_block(const SweepArgs& a, const StepIO& io, int storage, int ty, int zc,
                               hipStream_t s);

@@ -18,17 +18,30 @@
 // the receivers of the step before, which saves the second launch.
 //
 // us per step with a source and a receiver line, before (64 x 8 streaming
-// tiles) -> now: 64^3 22.5 -> 4.4, 128^3 23.4 -> 9.5, 160^3 29.5 -> 16.7,
-// 192^3 35.9 -> 23.3, 256^3 65.0 -> 52 (20-cell layer; 16 at 64^3); 256^3
-// without a layer 50.1 -> 37.3, 7.2 TB/s of its algorithmic bytes (a copy inside
-// that cache moves 8.3).
+// tiles) -> now: 64^3 22.5 -> 4.5, 128^3 23.4 -> 9.7, 160^3 29.5 -> 16.6, 192^3 35.9
+// -> 24, 256^3 65.0 -> 55 (20-cell layer; 16 at 64^3); 256^3 without a layer 50.1
+// -> 40 (7.2 TB/s of its algorithmic bytes on a zero field; a copy inside that
+// cache moves 8.3).  bf16 with two points per lane: 128^3 23.5 -> 8.2, 256^3 57 ->
+// 42.
+//
+// What bounds it now: up to about 96^3 the launch itself (2.5 us) and one pass of
+// memory latency; above, vector instructions in the layer and traffic to the
+// memory-side cache outside it (160^3: the vector units are busy 63 % of the
+// time).  Outside the z caps eta is the same in every plane of a block, so its
+// float64 sum, both denominators and their reciprocals are formed once per lane,
+// and the divisions continue from the reciprocals (div_by_rcp): 52 instead of 68
+// vector instructions per layer point.  Measured, us per step: float32 192^3
+// 25.9 -> 25.3, bf16 256^3 49.6 -> 46.7, stochastic bf16 256^3 55.7 -> 51.4.
 //
 // 4 x 4 rows and planes: 8 x 8 blocks read less halo, but hold more registers
 // with the layer's operands and leave fewer, longer workgroups (160^3 20.5).
 // Without a layer the registers are not short and 8 x 8 wins on larger grids.
+// Lanes laid out as 32 columns x 2 rows in tiles that hold an x wall, which pays
+// in the streaming kernel, does not here (192^3 23.0 either way).
 #include <algorithm>
 
 #include "wave_internal.h"
+#include "wave_pair.h"
 #include "wave_point.h"
 
 namespace wave {
@@ -53,7 +66,8 @@ struct BlockAt {
 };
 
 // One wavefront's row of the block.  EM as in the streaming kernel: 0 no layer
-// point, 1 eta array, 2 tables.  FULL: the block has all ZC planes.  NTP: the
+// point, 1 eta array, 2 tables, and 3 tables outside the z caps, where the
+// profile's z term is 0 and eta is the same in every plane.  FULL: the block has all ZC planes.  NTP: the
 // state is larger than the memory-side cache, and all but u^n goes around it.
 template <class S, int TY, int ZC, int EM, bool FULL, bool NTP>
 __device__ __forceinline__ void block_rows(const SweepArgs& a, const StepIO& io,
@@ -138,7 +152,7 @@ __device__ __forceinline__ void block_rows(const SweepArgs& a, const StepIO& io,
   float er[ZC + 2], ex0[ZC], ex1[ZC], ey0[ZC], ey1[ZC];
   double tsc = 0.0, tz[ZC];
   float dqx = 0.0f, dqy = 0.0f, dz[ZC];
-  if (EM == 2) {
+  if (EM >= 2) {
     const double* tx = a.etab + 1;
     const double* ty = tx + a.nx + 2;
     const BCDouble* tzt = (const BCDouble*)(ty + a.ny + 2) + b.zb;
@@ -149,7 +163,7 @@ __device__ __forceinline__ void block_rows(const SweepArgs& a, const StepIO& io,
     dqy = a.etq[a.nx + yc];
 #pragma unroll
     for (int k = 0; k < ZC; ++k) {
-      tz[k] = tzt[pl(k) - kR];
+      if (EM == 2) tz[k] = tzt[pl(k) - kR];
       dz[k] = dqzt[pl(k) - kR];
     }
   }
@@ -190,7 +204,8 @@ __device__ __forceinline__ void block_rows(const SweepArgs& a, const StepIO& io,
   // offsets of ds_read2 without an address add each
   int xbase = (wv * ZC) * (kTX + 2 * kR) + kR + lane;
   asm volatile("" : "+v"(xbase));
-  float res[ZC];
+  float res[ZC], et[ZC], n1[ZC], n2[ZC];
+  if (EM == 3) et[0] = lay ? (float)(a.dt * tsc) : 0.0f;
 #pragma unroll
   for (int k = 0; k < ZC; ++k) {
     const float* xr = &sm.xr[0][0][0] + xbase + k * (kTX + 2 * kR);
@@ -207,27 +222,56 @@ __device__ __forceinline__ void block_rows(const SweepArgs& a, const StepIO& io,
       lap = __builtin_fmaf(a.c[8 + m], q[kR + k + m] + q[kR + k - m], lap);
     lap = __builtin_fmaf(a.ce, c, lap);
     if (LAYER) {
-      float e, gx, gy, gz;
+      float gx, gy, gz;
       if (EARR) {
-        e = er[k + 1];
+        et[k] = er[k + 1];
         gx = (ex1[k] - ex0[k]) * a.q[0];
         gy = (ey1[k] - ey0[k]) * a.q[1];
         gz = (er[k + 2] - er[k]) * a.q[2];
       } else {
-        const float et = (float)(a.dt * (tsc + tz[k]));
-        e = lay ? et : 0.0f;
+        if (EM == 2) et[k] = lay ? (float)(a.dt * (tsc + tz[k])) : 0.0f;
         gx = dqx;
         gy = dqy;
         gz = dz[k];
       }
       // outside the layer eta and phi read 0 and the store of phi is dropped
-      res[k] = upd_layer(c, pv[k], vv[k], lap, e, ph[k]);
-      const float nph = upd_phi(ph[k], e, gx, xr[1] - xr[-1], gy, yr[kTX] - yr[-kTX], gz,
-                                q[kR + k + 1] - q[kR + k - 1]);
-      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(nph), rph,
-                                            (int)(FULL || k < nzb ? fo : kOOB), (int)(pl(k) * p4), kBst);
+      n1[k] = layer_num(c, pv[k], vv[k], lap, et[EM == 3 ? 0 : k], ph[k]);
+      n2[k] = phi_num(ph[k], gx, xr[1] - xr[-1], gy, yr[kTX] - yr[-kTX], gz,
+                      q[kR + k + 1] - q[kR + k - 1]);
     } else {
       res[k] = upd_inner(c, pv[k], vv[k], lap);
+    }
+  }
+  if (LAYER) {
+    float least = __builtin_fminf(__builtin_fabsf(n1[0]), __builtin_fabsf(n2[0]));
+#pragma unroll
+    for (int k = 1; k < ZC; ++k)
+      least = __builtin_fminf(least, __builtin_fminf(__builtin_fabsf(n1[k]), __builtin_fabsf(n2[k])));
+    if (__any(lay && least < kDivMin)) {
+#pragma unroll
+      for (int k = 0; k < ZC; ++k) {
+        const float e = et[EM == 3 ? 0 : k];
+        n1[k] = n1[k] / layer_den(e);
+        n2[k] = n2[k] / phi_den(e);
+      }
+    } else {
+      float r1 = 0.0f, r2 = 0.0f;
+#pragma unroll
+      for (int k = 0; k < ZC; ++k) {
+        const float e = et[EM == 3 ? 0 : k], d1 = layer_den(e), d2 = phi_den(e);
+        if (EM != 3 || k == 0) {
+          r1 = rcp_of(d1);
+          r2 = rcp_of(d2);
+        }
+        n1[k] = div_by_rcp(n1[k], d1, r1);
+        n2[k] = div_by_rcp(n2[k], d2, r2);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < ZC; ++k) {
+      res[k] = q[kR + k] + n1[k];
+      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(n2[k]), rph,
+                                            (int)(FULL || k < nzb ? fo : kOOB), (int)(pl(k) * p4), kBst);
     }
   }
 
@@ -262,8 +306,259 @@ __device__ __forceinline__ void block_rows(const SweepArgs& a, const StepIO& io,
   }
 }
 
+// The 64 x 8 x 4 block with two x-adjacent points per lane: a wavefront owns two
+// rows of 32 pairs.  For 16-bit storage, whose one-point loads and stores move 2
+// bytes per lane: half the memory and LDS instructions of the 4 x 4 block
+// (f16 333 x 256 x 272, 20-cell layer, 73 -> 66 us per step; bf16 256^3 50 -> 42).
+// float32 gains nothing (192^3 24.3 -> 27.4: 109 registers, 4 wavefronts per SIMD),
+// and stochastic rounding spills.  EM 0, 2 or 3.
+constexpr int kDY = 8, kDZ = 4;
+struct DuoLds {
+  float xr[kDY][kDZ][kTX + 2 * kR];
+  float yz[kDZ][kDY + 2 * kR][kTX];
+};
+
+template <class S, int EM, bool FULL>
+__device__ __forceinline__ void duo_rows(const SweepArgs& a, const StepIO& io, DuoLds& sm,
+                                         const BlockAt& b, const bool (&lay)[2]) {
+  using T = typename S::T;
+  using IO = PairIO<S>;
+  constexpr int NT = 32 * kDY;
+  constexpr int NXE = kR * kDY * kDZ;  // x-halo pairs of the block
+  constexpr uint32_t ES = sizeof(T);
+  constexpr bool LAYER = EM != 0;
+  constexpr int ZC = kDZ;
+  static_assert(2 * kR * (kTX / 2) == NT && NXE <= NT, "one y-halo pair per thread and plane");
+
+  const int tid = threadIdx.x;
+  const int col = 2 * (tid & 31), row = tid >> 5;
+  const int x = b.x0 + col, y = b.y0 + row;
+  const int nzb = FULL ? ZC : b.nzb;
+  auto pl = [&](int k) -> uint32_t { return (uint32_t)(kR + (FULL ? k : min(k, nzb - 1))); };
+  const int64_t Q = a.plane;
+  const int P = a.pitch;
+  const uint32_t pe = (uint32_t)Q * ES, p4 = (uint32_t)Q * 4u;
+  const int64_t w0 = (int64_t)(b.zb - kR) * Q - (int64_t)kR * P;
+  const uint32_t nwin = (uint32_t)(nzb + 2 * kR);
+  const auto ru = rsrc_at(static_cast<const T*>(a.cur) + w0, nwin * pe);
+  const auto rn = rsrc_at(static_cast<T*>(a.nxt) + w0, nwin * pe);
+  const auto rv = rsrc_at(a.vp + w0, nwin * p4);
+  const auto rph = rsrc_at(LAYER ? (const void*)(a.phi + w0) : nullptr, LAYER ? nwin * p4 : 0u);
+  // a pair past the grid touches nothing; one whose second point is the first
+  // ghost column stores that point's 0
+  const bool valid = x < a.nx && y < a.ny, valid1 = x + 1 < a.nx;
+  const uint32_t ro = (uint32_t)((y + kR) * P + x);
+  const uint32_t vo = valid ? ro * ES : kOOB, vo4 = valid ? ro * 4u : kOOB;
+  const uint32_t fo = LAYER && (lay[0] || lay[1]) ? vo4 : kOOB;
+
+  uint32_t smask = 0;
+#pragma unroll
+  for (int s = 0; s < kStepSrc; ++s)
+    if (io.sz[s] >= b.zb && io.sz[s] < b.zb + nzb && io.sy[s] >= b.y0 && io.sy[s] < b.y0 + kDY &&
+        io.sx[s] >= b.x0 && io.sx[s] < b.x0 + kTX)
+      smask |= 1u << s;
+
+  f32x2 q[ZC + 2 * kR], hy[ZC], hx, vv[ZC], pv[ZC], ph[ZC];
+#pragma unroll
+  for (int k = 0; k < ZC; ++k)
+    q[kR + k] = IO::ld(ru, vo, (uint32_t)(FULL ? kR + k : min(kR + k, nzb + 2 * kR - 1)) * pe);
+  const int gy = row < kR ? b.y0 - kR + row : b.y0 + kDY + (row - kR);  // halo row
+  const uint32_t ho = gy >= 0 && gy < a.ny && x < a.nx ? (uint32_t)((gy + kR) * P + x) * ES : kOOB;
+#pragma unroll
+  for (int k = 0; k < ZC; ++k) hy[k] = IO::ld(ru, ho, pl(k) * pe);
+  const int hp = tid & 3, hr = (tid >> 2) % kDY, hk = tid / (4 * kDY);
+  const int gx = hp < 2 ? b.x0 - kR + 2 * hp : b.x0 + kTX + 2 * (hp - 2);
+  const bool hin = hk < nzb && gx >= 0 && gx < a.nx && b.y0 + hr < a.ny;
+  hx = IO::ld(ru, hin ? (uint32_t)((b.y0 + hr + kR) * P + gx) * ES + (uint32_t)(kR + hk) * pe : kOOB, 0u);
+#pragma unroll
+  for (int j = 0; j < kR; ++j) {
+    q[j] = IO::ld(ru, vo, (uint32_t)j * pe);
+    q[kR + ZC + j] =
+        IO::ld(ru, vo, (uint32_t)(FULL ? kR + ZC + j : min(kR + ZC + j, nzb + 2 * kR - 1)) * pe);
+  }
+#pragma unroll
+  for (int k = 0; k < ZC; ++k) {
+    vv[k] = ld_f32x2(rv, vo4, pl(k) * p4, false);
+    pv[k] = IO::ld(rn, vo, pl(k) * pe);
+    if (LAYER) ph[k] = ld_f32x2(rph, fo, pl(k) * p4, false);
+  }
+  double tsc[2] = {0.0, 0.0}, tz[ZC];
+  float dqx[2] = {0.0f, 0.0f}, dqy = 0.0f, dz[ZC];
+  if (LAYER) {
+    const double* tx = a.etab + 1;
+    const double* ty = tx + a.nx + 2;
+    const BCDouble* tzt = (const BCDouble*)(ty + a.ny + 2) + b.zb;
+    const BCFloat* dqzt = (const BCFloat*)(a.etq + a.nx + a.ny) + b.zb;
+    const int xc = min(x, a.nx - 1), xd = min(x + 1, a.nx - 1), yc = min(y, a.ny - 1);
+    tsc[0] = tx[xc] + ty[yc];
+    tsc[1] = tx[xd] + ty[yc];
+    dqx[0] = a.etq[xc];
+    dqx[1] = a.etq[xd];
+    dqy = a.etq[a.nx + yc];
+#pragma unroll
+    for (int k = 0; k < ZC; ++k) {
+      if (EM == 2) tz[k] = tzt[pl(k) - kR];
+      dz[k] = dqzt[pl(k) - kR];
+    }
+  }
+
+  const int hrow = row < kR ? row : kDY + row;
+#pragma unroll
+  for (int k = 0; k < ZC; ++k) {
+    *reinterpret_cast<f32x2*>(&sm.yz[k][kR + row][col]) = q[kR + k];
+    *reinterpret_cast<f32x2*>(&sm.xr[row][k][kR + col]) = q[kR + k];
+    *reinterpret_cast<f32x2*>(&sm.yz[k][hrow][col]) = hy[k];
+  }
+  if (tid < NXE) *reinterpret_cast<f32x2*>(&sm.xr[hr][hk][hp < 2 ? 2 * hp : kTX + 2 * hp]) = hx;
+  __syncthreads();
+
+  // the x rows' base in a register of its own: the reads then fit the 8-bit
+  // offsets of ds_read2 without an address add each
+  int xbase = (row * ZC) * (kTX + 2 * kR) + kR + col;
+  asm volatile("" : "+v"(xbase));
+  float res[ZC][2], et[ZC][2], n2[ZC][2];
+  if (EM == 3)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) et[0][i] = lay[i] ? (float)(a.dt * tsc[i]) : 0.0f;
+#pragma unroll
+  for (int k = 0; k < ZC; ++k) {
+    const float* xr = &sm.xr[0][0][0] + xbase + k * (kTX + 2 * kR);
+    const float* yr = &sm.yz[k][kR + row][col];
+    const f32x2 cc = q[kR + k];
+    const f32x2 a4 = *reinterpret_cast<const f32x2*>(xr - 4), a2 = *reinterpret_cast<const f32x2*>(xr - 2);
+    const f32x2 b2 = *reinterpret_cast<const f32x2*>(xr + 2), b4 = *reinterpret_cast<const f32x2*>(xr + 4);
+    const float xv[10] = {a4[0], a4[1], a2[0], a2[1], cc[0], cc[1], b2[0], b2[1], b4[0], b4[1]};
+    f32x2 ym[kR], yp[kR];
+#pragma unroll
+    for (int m = 1; m <= kR; ++m) {
+      ym[m - 1] = *reinterpret_cast<const f32x2*>(yr - m * kTX);
+      yp[m - 1] = *reinterpret_cast<const f32x2*>(yr + m * kTX);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const float c = cc[i];
+      float lap = a.c[0] * c;
+#pragma unroll
+      for (int m = 1; m <= kR; ++m) lap = __builtin_fmaf(a.c[m], xv[4 + i + m] + xv[4 + i - m], lap);
+#pragma unroll
+      for (int m = 1; m <= kR; ++m) lap = __builtin_fmaf(a.c[4 + m], yp[m - 1][i] + ym[m - 1][i], lap);
+#pragma unroll
+      for (int m = 1; m <= kR; ++m)
+        lap = __builtin_fmaf(a.c[8 + m], q[kR + k + m][i] + q[kR + k - m][i], lap);
+      lap = __builtin_fmaf(a.ce, c, lap);
+      if (LAYER) {
+        // a pair's inner point: eta and phi count as 0, phi is written back
+        if (EM == 2) et[k][i] = lay[i] ? (float)(a.dt * (tsc[i] + tz[k])) : 0.0f;
+        const float phv = lay[i] ? ph[k][i] : 0.0f;
+        res[k][i] = layer_num(c, pv[k][i], vv[k][i], lap, et[EM == 3 ? 0 : k][i], phv);
+        n2[k][i] = phi_num(phv, dqx[i], xv[5 + i] - xv[3 + i], dqy, yp[0][i] - ym[0][i], dz[k],
+                           q[kR + k + 1][i] - q[kR + k - 1][i]);
+      } else {
+        res[k][i] = upd_inner(c, pv[k][i], vv[k][i], lap);
+      }
+    }
+  }
+  if (LAYER) {
+    bool small = false;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      float least = __builtin_fminf(__builtin_fabsf(res[0][i]), __builtin_fabsf(n2[0][i]));
+#pragma unroll
+      for (int k = 1; k < ZC; ++k)
+        least = __builtin_fminf(least, __builtin_fminf(__builtin_fabsf(res[k][i]), __builtin_fabsf(n2[k][i])));
+      small = small || (lay[i] && least < kDivMin);
+    }
+    const bool exact = __any(small);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      if (exact) {
+#pragma unroll
+        for (int k = 0; k < ZC; ++k) {
+          const float e = et[EM == 3 ? 0 : k][i];
+          res[k][i] = res[k][i] / layer_den(e);
+          n2[k][i] = n2[k][i] / phi_den(e);
+        }
+      } else {
+        float r1 = 0.0f, r2 = 0.0f;
+#pragma unroll
+        for (int k = 0; k < ZC; ++k) {
+          const float e = et[EM == 3 ? 0 : k][i], d1 = layer_den(e), d2 = phi_den(e);
+          if (EM != 3 || k == 0) {
+            r1 = rcp_of(d1);
+            r2 = rcp_of(d2);
+          }
+          res[k][i] = div_by_rcp(res[k][i], d1, r1);
+          n2[k][i] = div_by_rcp(n2[k][i], d2, r2);
+        }
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < ZC; ++k) {
+      res[k][0] = q[kR + k][0] + res[k][0];
+      res[k][1] = q[kR + k][1] + res[k][1];
+      __builtin_amdgcn_raw_buffer_store_b64(
+          u32x2{__float_as_uint(lay[0] ? n2[k][0] : ph[k][0]), __float_as_uint(lay[1] ? n2[k][1] : ph[k][1])},
+          rph, (int)(FULL || k < nzb ? fo : kOOB), (int)(pl(k) * p4), kStThrough);
+    }
+  }
+
+  const uint32_t srkey = S::kSR ? pcg_hash((uint32_t)a.step) : 0u;
+  T ev[ZC][2];
+#pragma unroll
+  for (int k = 0; k < ZC; ++k) {
+    if constexpr (S::kSR) {  // x is even: both points take their bits from one word
+      const uint32_t wd = sr_word(srkey, a.nx, a.ny, x, y, b.zb + k);
+      ev[k][0] = f32_to_bf16_sr(res[k][0], wd);
+      ev[k][1] = f32_to_bf16_sr(res[k][1], wd >> 16);
+    } else {
+      ev[k][0] = S::enc(res[k][0]);
+      ev[k][1] = S::enc(res[k][1]);
+    }
+  }
+  if (smask) {
+#pragma unroll
+    for (int s = 0; s < kStepSrc; ++s) {
+      if (!(smask >> s & 1)) continue;
+#pragma unroll
+      for (int k = 0; k < ZC; ++k)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+          if (io.sz[s] == b.zb + k && io.sy[s] == y && io.sx[s] == x + i)
+            ev[k][i] = S::enc(__builtin_fmaf(vv[k][i], io.sw[s], S::cvt(ev[k][i])));
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < ZC; ++k) {
+    const int so = (int)(pl(k) * pe), vk = (int)(FULL || k < nzb ? vo : kOOB);
+    const T e1 = valid1 ? ev[k][1] : (T)0;
+    if constexpr (sizeof(T) == 4)
+      __builtin_amdgcn_raw_buffer_store_b64(
+          u32x2{__builtin_bit_cast(uint32_t, ev[k][0]), __builtin_bit_cast(uint32_t, e1)}, rn, vk, so, kStThrough);
+    else
+      __builtin_amdgcn_raw_buffer_store_b32(
+          (uint32_t)__builtin_bit_cast(uint16_t, ev[k][0]) | ((uint32_t)__builtin_bit_cast(uint16_t, e1) << 16),
+          rn, vk, so, kStThrough);
+  }
+}
+
 __device__ __forceinline__ int div_by(int n, int d, uint32_t m) {
   return d == 1 ? n : (int)__umulhi((uint32_t)n, m);
+}
+
+// Tile and layer of block `at` of XCD xcd; false: slab padding.  An XCD takes one
+// slab of tile rows through the layers of blocks, so neighbouring blocks read
+// their halos from one L2 (8 % faster at 256^3 than a contiguous run of layers
+// per XCD).  Where the tile rows do not divide by 8 the slabs differ by a row;
+// in the upper half of the layers every XCD takes the next one's, which evens
+// them out.
+__device__ __forceinline__ bool block_at(const BlockGrid& g, int xcd, int at, int* tx, int* ty,
+                                         int* zl) {
+  const int t2 = div_by(at, g.tiles_x, g.mx);
+  *tx = at - t2 * g.tiles_x;
+  *zl = div_by(t2, g.slab, g.mslab);
+  const int k = (xcd + (*zl >= g.half ? 1 : 0)) & 7;
+  *ty = (k * g.tiles_y >> 3) + t2 - *zl * g.slab;
+  return *ty < ((k + 1) * g.tiles_y >> 3);
 }
 
 // Block `at` of XCD xcd.  LM: the layer's update, 0 damping off, 1 eta array,
@@ -272,17 +567,12 @@ template <class S, int TY, int ZC, int LM, bool NTP>
 __device__ __forceinline__ void block_sweep(const SweepArgs& a, const StepIO& io,
                                             BlockLds<TY, ZC>& sm, const BlockGrid& g, int xcd,
                                             int at) {
-  // An XCD takes one slab of tile rows through all layers of blocks, so
-  // neighbouring blocks read their halos from one L2 (8 % faster at 256^3
-  // than a contiguous run of layers per XCD).
-  const int t2 = div_by(at, g.tiles_x, g.mx);
-  const int zl = div_by(t2, g.slab, g.mslab);
-  const int ty = xcd * g.slab + t2 - zl * g.slab;
-  if (ty >= g.tiles_y) return;
+  int tx, ty, zl;
+  if (!block_at(g, xcd, at, &tx, &ty, &zl)) return;
   constexpr bool damp = LM != 0;
   const ChunkInfo c = chunk_of(zl, a.nz, a.w, ZC, damp);
   BlockAt b;
-  b.x0 = (at - t2 * g.tiles_x) * kTX;
+  b.x0 = tx * kTX;
   b.y0 = ty * TY;
   b.zb = c.zb;
   b.nzb = c.ze - c.zb;
@@ -290,17 +580,68 @@ __device__ __forceinline__ void block_sweep(const SweepArgs& a, const StepIO& io
   const int y = b.y0 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const bool lay = damp && x < a.nx && y < a.ny &&
                    (c.cap || x < a.w || x >= a.nx - a.w || y < a.w || y >= a.ny - a.w);
+  const bool none = LM == 0 || !__any(lay);
   if (b.nzb == ZC) {
-    if (LM == 0 || !__any(lay))
+    if (none)
       block_rows<S, TY, ZC, 0, true, NTP>(a, io, sm, b, false);
+    else if (LM == 2 && !c.cap)
+      block_rows<S, TY, ZC, 3, true, NTP>(a, io, sm, b, lay);
     else
       block_rows<S, TY, ZC, LM, true, NTP>(a, io, sm, b, lay);
   } else {
-    if (LM == 0 || !__any(lay))
+    if (none)
       block_rows<S, TY, ZC, 0, false, NTP>(a, io, sm, b, false);
     else
       block_rows<S, TY, ZC, LM, false, NTP>(a, io, sm, b, lay);
   }
+}
+
+// The same for blocks with two points per lane.
+template <class S, int LM>
+__device__ __forceinline__ void duo_sweep(const SweepArgs& a, const StepIO& io, DuoLds& sm,
+                                          const BlockGrid& g, int xcd, int at) {
+  int tx, ty, zl;
+  if (!block_at(g, xcd, at, &tx, &ty, &zl)) return;
+  constexpr bool damp = LM != 0;
+  const ChunkInfo c = chunk_of(zl, a.nz, a.w, kDZ, damp);
+  BlockAt b;
+  b.x0 = tx * kTX;
+  b.y0 = ty * kDY;
+  b.zb = c.zb;
+  b.nzb = c.ze - c.zb;
+  const int y = b.y0 + (int)(threadIdx.x >> 5);
+  bool lay[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int x = b.x0 + 2 * (int)(threadIdx.x & 31) + i;
+    lay[i] = damp && x < a.nx && y < a.ny &&
+             (c.cap || x < a.w || x >= a.nx - a.w || y < a.w || y >= a.ny - a.w);
+  }
+  const bool none = LM == 0 || !__any(lay[0] || lay[1]);
+  if (b.nzb == kDZ) {
+    if (none)
+      duo_rows<S, 0, true>(a, io, sm, b, lay);
+    else if (LM == 2 && !c.cap)
+      duo_rows<S, 3, true>(a, io, sm, b, lay);
+    else
+      duo_rows<S, LM, true>(a, io, sm, b, lay);
+  } else {
+    if (none)
+      duo_rows<S, 0, false>(a, io, sm, b, lay);
+    else
+      duo_rows<S, LM, false>(a, io, sm, b, lay);
+  }
+}
+
+template <class S, int LM>
+__global__ __launch_bounds__(256, 4) void k_sweep_duo(SweepArgs a, StepIO io, BlockGrid g) {
+  __shared__ __attribute__((aligned(16))) DuoLds sm;
+  const int slot = blockIdx.x >> 3;
+  if (slot >= g.per_xcd) {
+    record_row<S>(a, io, (blockIdx.x - 8 * g.per_xcd) * 256 + threadIdx.x);
+    return;
+  }
+  duo_sweep<S, LM>(a, io, sm, g, blockIdx.x & 7, (a.step & 1) ? g.per_xcd - 1 - slot : slot);
 }
 
 template <class S, int TY, int ZC, int LM, bool NTP>
@@ -319,10 +660,10 @@ __global__ __launch_bounds__(64 * TY, 4) void k_sweep_block(SweepArgs a, StepIO 
 
 // Several members of a batch in one launch.  The sweep's arguments come from
 // the batch's table, everything that changes from step to step by value.
-template <class S, int LM>
+template <class S, int LM, bool DUO>
 __global__ __launch_bounds__(256, 4) void k_sweep_block_batch(const BatchShot* __restrict__ shots,
                                                               BlockBatch bb) {
-  __shared__ BlockLds<4, 4> sm;
+  __shared__ __attribute__((aligned(16))) std::conditional_t<DUO, DuoLds, BlockLds<4, 4>> sm;
   const int bid = (int)order_block(blockIdx.x, gridDim.x, bb.back);
   int m = 0;
   for (int i = 1; i < bb.n; ++i)
@@ -337,7 +678,10 @@ __global__ __launch_bounds__(256, 4) void k_sweep_block_batch(const BatchShot* _
     record_row<S>(a, e.io, (local - 8 * e.g.per_xcd) * 256 + threadIdx.x);
     return;
   }
-  block_sweep<S, 4, 4, LM, false>(a, e.io, sm, e.g, local & 7, local >> 3);
+  if constexpr (DUO)
+    duo_sweep<S, LM>(a, e.io, sm, e.g, local & 7, local >> 3);
+  else
+    block_sweep<S, 4, 4, LM, false>(a, e.io, sm, e.g, local & 7, local >> 3);
 }
 
 template <class S>
@@ -354,7 +698,9 @@ bool block_grid(const SweepArgs& a, int ty, int zc, BlockGrid* g) {
   g->tiles_x = cdiv(a.nx, kTX);
   g->tiles_y = cdiv(a.ny, ty);
   g->slab = cdiv(g->tiles_y, 8);
-  const int64_t n = (int64_t)g->tiles_x * g->slab * chunk_count(a.nz, a.w, zc, a.damping != 0);
+  const int layers = chunk_count(a.nz, a.w, zc, a.damping != 0);
+  g->half = cdiv(layers, 2);
+  const int64_t n = (int64_t)g->tiles_x * g->slab * layers;
   if ((int64_t)(zc + 2 * kR) * a.plane * 4 > kWindowMax ||
       n * std::max(g->tiles_x, g->slab) >= (int64_t(1) << 32) || n > 0x07ffffff)
     return false;
@@ -375,12 +721,24 @@ hipError_t block_t(const SweepArgs& a, const StepIO& io, hipStream_t st) {
   return hipGetLastError();
 }
 
+template <class S, int LM>
+hipError_t duo_t(const SweepArgs& a, const StepIO& io, hipStream_t st) {
+  BlockGrid g;
+  if (!block_grid(a, kDY, kDZ, &g)) return hipErrorInvalidValue;
+  const int rec = io.nrec > 0 ? cdiv(io.nrec, 256) : 0;
+  hipLaunchKernelGGL((k_sweep_duo<S, LM>), dim3((unsigned)(8 * g.per_xcd + rec)), dim3(256), 0, st, a, io, g);
+  return hipGetLastError();
+}
+
 template <class S>
 hipError_t block_s(const SweepArgs& a, const StepIO& io, int ty, int zc, bool nt, hipStream_t st) {
   if (ty == 4 && zc == 4)
     return a.eta       ? block_t<S, 4, 4, 1, false>(a, io, st)
            : a.damping ? block_t<S, 4, 4, 2, false>(a, io, st)
                        : block_t<S, 4, 4, 0, false>(a, io, st);
+  if constexpr (sizeof(typename S::T) == 2 && !S::kSR) {
+    if (ty == kDY && zc == kDZ && !a.eta) return a.damping ? duo_t<S, 2>(a, io, st) : duo_t<S, 0>(a, io, st);
+  }
   if constexpr (!S::kSR) {
     if (ty == 8 && zc == 8 && !a.damping)
       return nt ? block_t<S, 8, 8, 0, true>(a, io, st) : block_t<S, 8, 8, 0, false>(a, io, st);
@@ -391,7 +749,7 @@ hipError_t block_s(const SweepArgs& a, const StepIO& io, int ty, int zc, bool nt
 }  // namespace
 
 bool block_config_supported(int ty, int zc, const SweepArgs& a, int storage) {
-  const bool cfg = (ty == 4 && zc == 4) || (ty == 8 && zc == 8 && !a.damping && storage != 3);
+  const bool cfg = (ty == 4 && zc == 4) || (ty == kDY && zc == kDZ && !a.eta && (storage == 1 || storage == 2)) || (ty == 8 && zc == 8 && !a.damping && storage != 3);
   BlockGrid g;
   return cfg && block_grid(a, ty, zc, &g);
 }
@@ -407,10 +765,16 @@ void block_default(const SweepArgs& a, int storage, int* ty, int* zc) {
   const int64_t bytes =
       sweep_footprint(a.nx, a.ny, a.nz, a.w, a.damping != 0, a.eta != nullptr, es);
   *ty = *zc = 0;
-  if (!a.damping && storage != 3 && bytes > (es == 4 ? 240 : 24) * 1000000LL)
+  const bool duo = es == 2 && storage != 3 && !a.eta && bytes > 10 * 1000000LL &&
+                   bytes <= (a.damping ? 360 : 280) * 1000000LL;
+  if (duo) {
+    *ty = kDY;
+    *zc = kDZ;
+  } else if (!a.damping && storage != 3 && bytes > 240 * 1000000LL) {
     *ty = *zc = 8;
-  else if (bytes <= 280 * 1000000LL)
+  } else if (bytes <= 280 * 1000000LL) {
     *ty = *zc = 4;
+  }
   if (*ty && !block_config_supported(*ty, *zc, a, storage)) *ty = *zc = 0;
 }
 
@@ -431,31 +795,43 @@ hipError_t launch_sweep_block(const SweepArgs& a, const StepIO& io, int storage,
   return hipErrorInvalidValue;
 }
 
-int block_batch_grid(const SweepArgs& a, int nrec, BlockGrid* g) {
-  if (!block_grid(a, 4, 4, g)) return 0;
+int block_batch_grid(const SweepArgs& a, bool duo, int nrec, BlockGrid* g) {
+  if (!block_grid(a, duo ? kDY : 4, duo ? kDZ : 4, g)) return 0;
   return 8 * (g->per_xcd + cdiv(cdiv(nrec, 256), 8));
 }
 
 template <class S>
-hipError_t block_batch_s(const BatchShot* shots, const BlockBatch& bb, int lm, hipStream_t st) {
+hipError_t block_batch_s(const BatchShot* shots, const BlockBatch& bb, int lm, bool duo,
+                         hipStream_t st) {
   const dim3 grid((unsigned)bb.begin[bb.n]);
+  if constexpr (sizeof(typename S::T) == 2 && !S::kSR) {
+    if (duo) {
+      if (lm == 0)
+        hipLaunchKernelGGL((k_sweep_block_batch<S, 0, true>), grid, dim3(256), 0, st, shots, bb);
+      else
+        hipLaunchKernelGGL((k_sweep_block_batch<S, 2, true>), grid, dim3(256), 0, st, shots, bb);
+      return hipGetLastError();
+    }
+  }
   if (lm == 0)
-    hipLaunchKernelGGL((k_sweep_block_batch<S, 0>), grid, dim3(256), 0, st, shots, bb);
+    hipLaunchKernelGGL((k_sweep_block_batch<S, 0, false>), grid, dim3(256), 0, st, shots, bb);
   else if (lm == 1)
-    hipLaunchKernelGGL((k_sweep_block_batch<S, 1>), grid, dim3(256), 0, st, shots, bb);
+    hipLaunchKernelGGL((k_sweep_block_batch<S, 1, false>), grid, dim3(256), 0, st, shots, bb);
   else
-    hipLaunchKernelGGL((k_sweep_block_batch<S, 2>), grid, dim3(256), 0, st, shots, bb);
+    hipLaunchKernelGGL((k_sweep_block_batch<S, 2, false>), grid, dim3(256), 0, st, shots, bb);
   return hipGetLastError();
 }
 
 hipError_t launch_sweep_block_batch(const BatchShot* shots, const BlockBatch& bb, int storage,
-                                    int lm, hipStream_t s) {
-  if (bb.n < 1 || bb.n > kBlockMembers || bb.begin[bb.n] < 1) return hipErrorInvalidValue;
+                                    int lm, bool duo, hipStream_t s) {
+  if (bb.n < 1 || bb.n > kBlockMembers || bb.begin[bb.n] < 1 ||
+      (duo && (lm == 1 || storage == 0 || storage == 3)))
+    return hipErrorInvalidValue;
   switch (storage) {
-    case 0: return block_batch_s<StF32>(shots, bb, lm, s);
-    case 1: return block_batch_s<StBF16>(shots, bb, lm, s);
-    case 2: return block_batch_s<StF16>(shots, bb, lm, s);
-    case 3: return block_batch_s<StBF16SR>(shots, bb, lm, s);
+    case 0: return block_batch_s<StF32>(shots, bb, lm, duo, s);
+    case 1: return block_batch_s<StBF16>(shots, bb, lm, duo, s);
+    case 2: return block_batch_s<StF16>(shots, bb, lm, duo, s);
+    case 3: return block_batch_s<StBF16SR>(shots, bb, lm, duo, s);
   }
   return hipErrorInvalidValue;
 }

@@ -165,21 +165,50 @@ __device__ __forceinline__ float upd_inner(float c, float pu, float vp, float la
   return c + __builtin_fmaf(vp, lap, c - pu);
 }
 
+// The layer update u' = u + layer_num / layer_den.
+__device__ __forceinline__ float layer_num(float c, float pu, float vp, float lap, float e,
+                                           float ph) {
+  return __builtin_fmaf(vp, lap + ph, __builtin_fmaf(-(e * e), c, c - pu));
+}
+__device__ __forceinline__ float layer_den(float e) { return __builtin_fmaf(2.0f, e, 1.0f); }
 __device__ __forceinline__ float upd_layer(float c, float pu, float vp, float lap, float e,
                                            float ph) {
-  const float t = __builtin_fmaf(-(e * e), c, c - pu);
-  const float num = __builtin_fmaf(vp, lap + ph, t);
-  return c + num / __builtin_fmaf(2.0f, e, 1.0f);
+  return c + layer_num(c, pu, vp, lap, e, ph) / layer_den(e);
 }
 
-// phi' from the products dq_a = fl32(de_a * q_a) of the eta differences and
-// 1 / (4 h_a^2), and the u differences du_a.
-__device__ __forceinline__ float upd_phi(float ph, float e, float dqx, float dux, float dqy,
-                                         float duy, float dqz, float duz) {
+// phi' = phi_num / phi_den from the products dq_a = fl32(de_a * q_a) of the eta
+// differences and 1 / (4 h_a^2), and the u differences du_a.
+__device__ __forceinline__ float phi_num(float ph, float dqx, float dux, float dqy, float duy,
+                                         float dqz, float duz) {
   float g = dqx * dux;
   g = __builtin_fmaf(dqy, duy, g);
   g = __builtin_fmaf(dqz, duz, g);
-  return (ph - g) / (1.0f + e);
+  return ph - g;
+}
+__device__ __forceinline__ float phi_den(float e) { return 1.0f + e; }
+__device__ __forceinline__ float upd_phi(float ph, float e, float dqx, float dux, float dqy,
+                                         float duy, float dqz, float duz) {
+  return phi_num(ph, dqx, dux, dqy, duy, dqz, duz) / phi_den(e);
+}
+
+// The two divisions of the layer update with the denominators' reciprocals at
+// hand.  These are the operations the compiler emits for n / d, one by one,
+// without its two operand scalings: v_div_scale passes operands through
+// unchanged for d in [1, 16) (the denominators are 1 + 2 eta and 1 + eta) and
+// |n| >= 2^-103, and for larger n nothing here can overflow before the quotient
+// does (fma rounds once).  So the bits are those of n / d wherever |n| >=
+// kDivMin, and v_div_fixup settles infinities and NaN; at d = 1 they are for
+// every n.  Callers take n / d itself where a layer point's n is smaller.
+constexpr float kDivMin = 0x1p-100f;
+__device__ __forceinline__ float rcp_of(float d) {
+  const float r = __builtin_amdgcn_rcpf(d);
+  return __builtin_fmaf(__builtin_fmaf(-d, r, 1.0f), r, r);
+}
+__device__ __forceinline__ float div_by_rcp(float n, float d, float r) {
+  float q = n * r;
+  q = __builtin_fmaf(__builtin_fmaf(-d, q, n), r, q);
+  q = __builtin_fmaf(__builtin_fmaf(-d, q, n), r, q);
+  return __builtin_amdgcn_div_fixupf(q, d, n);
 }
 
 // Buffer resource over memory starting at p (gfx9 family: stride 0, dword 3 =

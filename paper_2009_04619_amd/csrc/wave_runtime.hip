@@ -538,6 +538,7 @@ struct wave_batch::Group {
   int first, count;
   bool block;                 // the block kernel (lm: 0 damping off, 1 eta array, 2 tables)
   int lm;
+  bool duo;                   // two points per lane (8 x 4 blocks)
   int ry, nw;                 // otherwise the streaming tile (ry 0: two points per lane)
   bool eta_any;               // some member holds a per-point eta array
   std::vector<int64_t> prefix;        // workgroups of the first k members
@@ -643,21 +644,25 @@ void batch_drop_graphs(wave_batch* b) {
 }
 
 // Whether a member of a batch without a set tile runs the block kernel: its
-// own default launch does, and its sources fit one launch.
-bool batch_block_member(const wave_ctx* c) {
+// own default launch does, and its sources fit one launch.  *duo: with two
+// points per lane.
+bool batch_block_member(const wave_ctx* c, bool* duo) {
   int ty, zc;
   const wave::SweepArgs a = sweep_args(c);
   wave::block_default(a, kernel_storage(&c->d), &ty, &zc);
   wave::BlockGrid g;
-  return ty > 0 && c->nsrc <= wave::kStepSrc && member_bytes(c) <= 280 * 1000000LL &&
-         wave::block_batch_grid(a, c->nrec, &g) > 0;
+  *duo = ty == 8 && zc == 4;
+  return ty > 0 && c->nsrc <= wave::kStepSrc && (*duo || member_bytes(c) <= 280 * 1000000LL) &&
+         wave::block_batch_grid(a, *duo, c->nrec, &g) > 0;
 }
 
 // Launch order of a member in a batch without a set tile: members of one kind
 // can share a launch.
+constexpr int kStreamKind = 6;
 int batch_kind(const wave_ctx* c) {
   const int lm = !c->damp ? 0 : eta_array(&c->d) ? 1 : 2;
-  return batch_block_member(c) ? lm : 3 + (lm == 1 ? 1 : 0);
+  bool duo = false;
+  return batch_block_member(c, &duo) ? lm + (duo ? 3 : 0) : kStreamKind + (lm == 1 ? 1 : 0);
 }
 
 // Rebuild the member tables (static part) and the groups; targets are filled
@@ -675,7 +680,7 @@ void batch_layout(wave_batch* b) {
   for (size_t i = 0; i < b->members.size(); ++i) {
     wave_ctx* c = b->members[i];
     const int kind = b->by_size ? batch_kind(c) : 0;
-    const bool block = b->by_size && kind < 3;
+    const bool block = b->by_size && kind < kStreamKind;
     const int64_t mine = member_bytes(c);
     const bool fits = !b->groups.empty() &&
                       (!b->by_size || (kind == batch_kind(b->members[i - 1]) &&
@@ -686,7 +691,8 @@ void batch_layout(wave_batch* b) {
       g.first = (int)i;
       g.count = 0;
       g.block = block;
-      g.lm = kind;
+      g.lm = kind % 3;
+      g.duo = kind >= 3;
       g.ry = b->ry;
       g.nw = b->nw;
       if (b->by_size) {
@@ -712,7 +718,7 @@ void batch_layout(wave_batch* b) {
     e.inj = inject_args(c);
     if (g.block) {
       wave::BlockGrid bg;
-      g.prefix.push_back(g.prefix.back() + wave::block_batch_grid(e.sa, c->nrec, &bg));
+      g.prefix.push_back(g.prefix.back() + wave::block_batch_grid(e.sa, g.duo, c->nrec, &bg));
       g.grid.push_back(bg);
       continue;
     }
@@ -824,9 +830,9 @@ hipError_t batch_run_block(wave_batch* b, const wave_batch::Group& g) {
       a.cur = h[0].u[bb.m[0].cur];
       a.nxt = h[0].u[bb.m[0].cur ^ 1];
       a.step = bb.m[0].step;
-      e = wave::launch_sweep_block(a, bb.m[0].io, b->kstore, 4, 4, b->stream);
+      e = wave::launch_sweep_block(a, bb.m[0].io, b->kstore, g.duo ? 8 : 4, 4, b->stream);
     } else {
-      e = wave::launch_sweep_block_batch(b->d_shots + g.first, bb, b->kstore, g.lm, b->stream);
+      e = wave::launch_sweep_block_batch(b->d_shots + g.first, bb, b->kstore, g.lm, g.duo, b->stream);
     }
     if (e != hipSuccess) return e;
   }
@@ -1526,8 +1532,8 @@ int wave_set_kernel(wave_ctx* c, int32_t variant, int32_t ry, int32_t nw, int32_
   }
   if (variant == WAVE_KERNEL_BLOCK) {
     if (ry != 1 || !wave::block_config_supported(nw, zchunk, sweep_args(c), kernel_storage(&c->d)))
-      return fail(WAVE_EINVAL, "block kernel: rows_per_wave 1, 4 x 4 rows and planes (8 x 8 with damping off and "
-                               "no stochastic rounding), and planes small enough");
+      return fail(WAVE_EINVAL, "block kernel: rows_per_wave 1, 4 x 4 rows and planes (8 x 4 with 16-bit storage, "
+                               "8 x 8 with damping off; see wave.h), and planes small enough");
     c->variant = variant;
     c->shp[0] = 1;
     c->shp[1] = nw;

@@ -51,6 +51,8 @@ GRIDS = [  # nx, ny, nz, w, storage, damping, sources
     (65, 33, 11, 0, "f16", False, 5),
     (6, 6, 7, 3, "f32", True, 1),
     (1, 1, 1, 0, "bf16", False, 1),
+    (127, 50, 14, 4, "f16", True, 3),        # odd width: the last pair holds a ghost column
+    (64, 41, 30, 15, "bf16", True, 6),
 ]
 
 
@@ -66,7 +68,9 @@ def test_block_equals_oracle(W, grid):
     if not damping:
         expect["phi"] = np.zeros_like(expect["u"])
     sr = storage == "bf16sr"
-    for k in [(10, 1, 4, 4)] + ([] if damping or sr else [(10, 1, 8, 8)]):
+    kernels = [(10, 1, 4, 4)] + ([] if damping or sr else [(10, 1, 8, 8)]) + \
+        ([(10, 1, 8, 4)] if storage in ("bf16", "f16") else [])
+    for k in kernels:
         say(f"case block {k} grid {grid}")
         got = run(W, shot, calls, k, "bf16" if sr else storage, damping, sr)
         for key in ("u", "u_prev", "phi", "traces"):
@@ -87,10 +91,41 @@ def test_block_eta_array(W):
 def test_block_refusals(W):
     shot = synth.config_small_layered(40, 30, 20, 4, 4, seed=5)
     sh = W.shot_from_synth(shot)
-    for bad in ((10, 1, 8, 8), (10, 2, 4, 4), (10, 1, 4, 8), (10, 1, 4, 0), (10, 1, 0, 4), (10, 1, 4, -4)):
+    for bad in ((10, 1, 8, 8), (10, 2, 4, 4), (10, 1, 4, 8), (10, 1, 4, 0), (10, 1, 0, 4), (10, 1, 4, -4),
+                (10, 1, 8, 4)):
         assert W.wave_set_kernel(sh.ctx, *bad) == W.WAVE_EINVAL, bad
     assert W.wave_set_kernel(sh.ctx, 10, 1, 4, 4) == W.WAVE_OK
     sh.close()
+
+
+@pytest.mark.parametrize("storage,kernel", [("f32", (10, 1, 4, 4)), ("bf16", (10, 1, 8, 4))])
+def test_block_divisions_over_all_magnitudes(W, storage, kernel):
+    """Fields from zero and subnormal to 1e4: the layer's divisions take the
+    same bits as the direct kernel's, signs of zeros included."""
+    nx, ny, nz, w = 90, 41, 37, 12
+    shot = synth.config_small_layered(nx, ny, nz, w, 8, seed=31)
+    rng = np.random.default_rng(8)
+    state = []
+    for _ in range(3):
+        # magnitudes vary over blocks, so that whole wavefronts are tiny, mixed or ordinary
+        e = rng.uniform(-44.0, 4.0, (nz // 4 + 1, ny // 4 + 1, nx // 30 + 1))
+        e = np.kron(e, np.ones((4, 4, 30)))[:nz, :ny, :nx]
+        f = rng.standard_normal((nz, ny, nx)) * 10.0 ** e
+        f[rng.random((nz, ny, nx)) < 0.02] = 0.0
+        f[:, :, 40:60] = -0.0
+        state.append(f.astype(np.float32))
+    say(f"case block divisions {storage}")
+    outs = []
+    for k in (kernel, (0, 1, 1, 0)):
+        sh = W.shot_from_synth(shot, storage=storage, max_steps=8)
+        sh.set_kernel(*k)
+        for which, f in zip((W.WAVE_FIELD_U, W.WAVE_FIELD_UPREV, W.WAVE_FIELD_PHI), state):
+            sh.write(which, f)
+        sh.step(3)
+        outs.append([sh.read(i) for i in (W.WAVE_FIELD_U, W.WAVE_FIELD_UPREV, W.WAVE_FIELD_PHI)])
+        sh.close()
+    for x, y in zip(*outs):
+        assert np.isfinite(y).all() and np.array_equal(x.view(np.uint32), y.view(np.uint32))
 
 
 def _solo(W, args, n):
@@ -100,11 +135,11 @@ def _solo(W, args, n):
     return _state(W, sh)
 
 
-def _shot(W, nx, ny, nz, w, nsrc, eta, damping):
+def _shot(W, nx, ny, nz, w, nsrc, eta, damping, storage="f32"):
     rng = np.random.default_rng(nx + ny + nsrc)
     vel = rng.uniform(1500.0, 4000.0, (nz, ny, nx)).astype(np.float32)
     e = rng.uniform(0.0, 0.3, (nz, ny, nx)).astype(np.float32) if eta else None
-    sh = W.Shot(nx, ny, nz, w, 10.0, 10.0, 10.0, 9e-4, vel, eta=e, damping=damping, max_src=8,
+    sh = W.Shot(nx, ny, nz, w, 10.0, 10.0, 10.0, 9e-4, vel, eta=e, damping=damping, storage=storage, max_src=8,
                 max_rec=300, max_steps=16)
     for s in range(nsrc):
         p = (nx // 2, ny // 2, nz // 2) if s % 3 == 0 else tuple(int(rng.integers(0, n)) for n in (nx, ny, nz))
@@ -127,14 +162,20 @@ MANY = [(20 + 3 * i, 24, 18 + i, 3, 1, False, True) for i in range(19)]     # mo
 LARGE = [(224, 200, 208, 20, 1, False, True)] * 2 + [(64, 64, 64, 8, 1, False, True)]   # more than one group
 
 
+# 16-bit members on either side of the size where lanes take two points
+HALF = [(131, 112, 97, 9, 2, False, True, "bf16"), (128, 120, 90, 0, 1, False, False, "bf16"),
+        (60, 44, 30, 4, 3, False, True, "bf16"), (50, 44, 30, 4, 1, True, True, "bf16"),
+        (128, 112, 100, 20, 1, False, True, "bf16")]
+
+
 @pytest.mark.parametrize("graph", [0, 2])
-@pytest.mark.parametrize("members", [MIXED, MANY, LARGE], ids=["mixed", "many", "large"])
+@pytest.mark.parametrize("members", [MIXED, MANY, LARGE, HALF], ids=["mixed", "many", "large", "half"])
 def test_batch_by_size_equals_solo(W, members, graph):
     """A batch without a set tile: kinds of sweep side by side, members that
     stop early, runs that continue, several groups."""
     say(f"case batch by size, {len(members)} members, graph {graph}")
     n = [3 + (5 * i) % 7 for i in range(len(members))]
-    b = W.Batch(max_shots=len(members))
+    b = W.Batch(storage=members[0][7] if len(members[0]) > 7 else "f32", max_shots=len(members))
     b.set_graph(graph)
     shots = [_shot(W, *m) for m in members]
     for sh, k in zip(shots, n):
