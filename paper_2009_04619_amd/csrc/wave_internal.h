@@ -140,6 +140,7 @@ struct BlockGrid {
   int32_t half;      // first layer of the upper half
   int32_t per_xcd;   // blocks per XCD, slab padding included
   uint32_t mx, mslab;
+  int narrow;        // 32 x 8 x 4 points per block, else 64 wide
 };
 
 // One step of several members in one block-kernel launch, passed by value.

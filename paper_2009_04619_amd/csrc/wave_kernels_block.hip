@@ -1,4 +1,4 @@
-// wave_kernels_block.hip -- the sweep of small grids: one 64 x TY x ZC block of
+// wave_kernels_block.hip -- the sweep of small grids: one TW x TY x ZC block of
 // points per workgroup, all of its operands requested at once (paper Eq. 2-3
 // and the damping layer of Sec. III-B; the per-point arithmetic is
 // wave_point.h's, operand for operand).
@@ -37,7 +37,8 @@
 // with the layer's operands and leave fewer, longer workgroups (160^3 20.5).
 // Without a layer the registers are not short and 8 x 8 wins on larger grids.
 // Lanes laid out as 32 columns x 2 rows in tiles that hold an x wall, which pays
-// in the streaming kernel, does not here (192^3 23.0 either way).
+// in the streaming kernel, does not here (192^3 23.0 either way).  All tiles 32
+// wide (32 x 8 x 4) pay where 64-wide ones leave lanes idle: narrow_blocks.
 #include <algorithm>
 
 #include "wave_internal.h"
@@ -52,11 +53,12 @@ typedef const float __attribute__((address_space(4))) BCFloat;
 
 // Staged planes of a block.  yz: the centre planes with their y halo, rows of
 // 64 floats, so that one base register and the 64-float strides of ds_read2st64
-// reach every y neighbour of every plane; xr: each row with its x halo, the
-// planes of a row back to back.
-template <int TY, int ZC>
+// reach every y neighbour of every plane (also for 32-wide tiles: packed rows cost
+// 22 registers of addresses, 160^3 15.5 -> 16.4 us); xr: each row with its x halo,
+// the planes of a row back to back.
+template <int TW, int TY, int ZC>
 struct BlockLds {
-  float xr[TY][ZC][kTX + 2 * kR];
+  float xr[TY][ZC][TW + 2 * kR];
   float yz[ZC][TY + 2 * kR][kTX];
 };
 
@@ -65,28 +67,30 @@ struct BlockAt {
   int x0, y0, zb, nzb;
 };
 
-// One wavefront's row of the block.  EM as in the streaming kernel: 0 no layer
-// point, 1 eta array, 2 tables, and 3 tables outside the z caps, where the
-// profile's z term is 0 and eta is the same in every plane.  FULL: the block has all ZC planes.  NTP: the
-// state is larger than the memory-side cache, and all but u^n goes around it.
-template <class S, int TY, int ZC, int EM, bool FULL, bool NTP>
+// One wavefront's row of the block, or two rows of a 32-wide one.  EM as in the
+// streaming kernel: 0 no layer point, 1 eta array, 2 tables, and 3 tables outside
+// the z caps, where the profile's z term is 0 and eta is the same in every plane.
+// FULL: the block has all ZC planes.  NTP: the state is larger than the memory-side
+// cache, and all but u^n goes around it.
+template <class S, int TW, int TY, int ZC, int EM, bool FULL, bool NTP>
 __device__ __forceinline__ void block_rows(const SweepArgs& a, const StepIO& io,
-                                           BlockLds<TY, ZC>& sm, const BlockAt& b, bool lay) {
+                                           BlockLds<TW, TY, ZC>& sm, const BlockAt& b, bool lay) {
   using T = typename S::T;
-  constexpr int NT = 64 * TY;
-  constexpr int NYH = (2 * kR + TY - 1) / TY;  // y-halo rows per wavefront and plane
+  constexpr int NT = TW * TY;
+  constexpr int NYH = (2 * kR + TY - 1) / TY;  // y-halo cells per lane and plane
   constexpr int NXE = 2 * kR * TY * ZC;        // x-halo cells of the block
   constexpr int NXH = (NXE + NT - 1) / NT;
   constexpr uint32_t ES = sizeof(T);
   constexpr int kBst = NTP ? kSt : kStThrough;
   constexpr bool LAYER = EM != 0;
   constexpr bool EARR = EM == 1;
-  static_assert((2 * kR) % TY == 0, "whole y-halo rows per wavefront");
+  static_assert((2 * kR) % TY == 0 && NT % 64 == 0, "whole y-halo rows per pass");
 
   const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int x = b.x0 + lane, y = b.y0 + wv;
+  // column and row in the tile; 64-wide rows are wavefronts
+  const int col = tid & (TW - 1);
+  const int row = TW == 64 ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid / TW;
+  const int x = b.x0 + col, y = b.y0 + row;
   const int nzb = FULL ? ZC : b.nzb;
   // window index of plane k of the block (past a partial block's end: its last)
   auto pl = [&](int k) -> uint32_t { return (uint32_t)(kR + (FULL ? k : min(k, nzb - 1))); };
@@ -107,12 +111,14 @@ __device__ __forceinline__ void block_rows(const SweepArgs& a, const StepIO& io,
   const uint32_t vo = valid ? ro * ES : kOOB, vo4 = valid ? ro * 4u : kOOB;
   const uint32_t fo = LAYER && lay ? vo4 : kOOB;  // phi and eta: layer points only
 
-  // sources of this step in the wavefront's row
+  // sources of this step in the wavefront's rows
+  constexpr int RW = 64 / TW;
+  const int yw = TW == 64 ? y : __builtin_amdgcn_readfirstlane(y);
   uint32_t smask = 0;
 #pragma unroll
   for (int s = 0; s < kStepSrc; ++s)
-    if (io.sy[s] == y && io.sz[s] >= b.zb && io.sz[s] < b.zb + nzb && io.sx[s] >= b.x0 &&
-        io.sx[s] < b.x0 + kTX)
+    if (io.sy[s] >= yw && io.sy[s] < yw + RW && io.sz[s] >= b.zb && io.sz[s] < b.zb + nzb &&
+        io.sx[s] >= b.x0 && io.sx[s] < b.x0 + TW)
       smask |= 1u << s;
 
   // every load of the block: first what the staged planes hold, then the rest
@@ -122,7 +128,7 @@ __device__ __forceinline__ void block_rows(const SweepArgs& a, const StepIO& io,
     q[kR + k] = S::bld(ru, vo, (uint32_t)(FULL ? kR + k : min(kR + k, nzb + 2 * kR - 1)) * pe);
 #pragma unroll
   for (int i = 0; i < NYH; ++i) {
-    const int hr = wv + i * TY;  // halo row (wave-uniform)
+    const int hr = row + i * TY;  // halo row
     const int gy = hr < kR ? b.y0 - kR + hr : b.y0 + TY + (hr - kR);
     const uint32_t ho =
         gy >= 0 && gy < a.ny && x < a.nx ? (uint32_t)((gy + kR) * P + x) * ES : kOOB;
@@ -133,7 +139,7 @@ __device__ __forceinline__ void block_rows(const SweepArgs& a, const StepIO& io,
   for (int i = 0; i < NXH; ++i) {
     const int e = tid + i * NT;
     const int cc = e & (2 * kR - 1), rr = (e / (2 * kR)) % TY, k = e / (2 * kR * TY);
-    const int gx = cc < kR ? b.x0 - kR + cc : b.x0 + kTX + (cc - kR), gy = b.y0 + rr;
+    const int gx = cc < kR ? b.x0 - kR + cc : b.x0 + TW + (cc - kR), gy = b.y0 + rr;
     const bool in = k < nzb && gx >= 0 && gx < a.nx && gy < a.ny;
     hx[i] = S::bld(ru, in ? (uint32_t)((gy + kR) * P + gx) * ES + (uint32_t)(kR + k) * pe : kOOB, 0u);
   }
@@ -184,32 +190,32 @@ __device__ __forceinline__ void block_rows(const SweepArgs& a, const StepIO& io,
   // stage the centre planes with their x and y halos; one barrier
 #pragma unroll
   for (int k = 0; k < ZC; ++k) {
-    sm.yz[k][kR + wv][lane] = q[kR + k];
-    sm.xr[wv][k][kR + lane] = q[kR + k];
+    sm.yz[k][kR + row][col] = q[kR + k];
+    sm.xr[row][k][kR + col] = q[kR + k];
 #pragma unroll
     for (int i = 0; i < NYH; ++i) {
-      const int hr = wv + i * TY;
-      sm.yz[k][hr < kR ? hr : TY + hr][lane] = hy[i][k];
+      const int hr = row + i * TY;
+      sm.yz[k][hr < kR ? hr : TY + hr][col] = hy[i][k];
     }
   }
 #pragma unroll
   for (int i = 0; i < NXH; ++i) {
     const int e = tid + i * NT;
     const int cc = e & (2 * kR - 1), rr = (e / (2 * kR)) % TY, k = e / (2 * kR * TY);
-    if (NXE % NT == 0 || e < NXE) sm.xr[rr][k][cc < kR ? cc : kTX + cc] = hx[i];
+    if (NXE % NT == 0 || e < NXE) sm.xr[rr][k][cc < kR ? cc : TW + cc] = hx[i];
   }
   __syncthreads();
 
   // the x rows' base in a register of its own: the reads then fit the 8-bit
   // offsets of ds_read2 without an address add each
-  int xbase = (wv * ZC) * (kTX + 2 * kR) + kR + lane;
+  int xbase = (row * ZC) * (TW + 2 * kR) + kR + col;
   asm volatile("" : "+v"(xbase));
   float res[ZC], et[ZC], n1[ZC], n2[ZC];
   if (EM == 3) et[0] = lay ? (float)(a.dt * tsc) : 0.0f;
 #pragma unroll
   for (int k = 0; k < ZC; ++k) {
-    const float* xr = &sm.xr[0][0][0] + xbase + k * (kTX + 2 * kR);
-    const float* yr = &sm.yz[k][kR + wv][lane];
+    const float* xr = &sm.xr[0][0][0] + xbase + k * (TW + 2 * kR);
+    const float* yr = &sm.yz[k][kR + row][col];
     const float c = q[kR + k];
     float lap = a.c[0] * c;
 #pragma unroll
@@ -292,7 +298,7 @@ __device__ __forceinline__ void block_rows(const SweepArgs& a, const StepIO& io,
       if (!(smask >> s & 1)) continue;
 #pragma unroll
       for (int k = 0; k < ZC; ++k)
-        if (io.sz[s] == b.zb + k && io.sx[s] == x)
+        if (io.sz[s] == b.zb + k && io.sx[s] == x && (TW == 64 || io.sy[s] == y))
           ev[k] = S::enc(__builtin_fmaf(vv[k], io.sw[s], S::cvt(ev[k])));
     }
   }
@@ -563,36 +569,37 @@ __device__ __forceinline__ bool block_at(const BlockGrid& g, int xcd, int at, in
 
 // Block `at` of XCD xcd.  LM: the layer's update, 0 damping off, 1 eta array,
 // 2 tables.
-template <class S, int TY, int ZC, int LM, bool NTP>
+template <class S, int TW, int TY, int ZC, int LM, bool NTP>
 __device__ __forceinline__ void block_sweep(const SweepArgs& a, const StepIO& io,
-                                            BlockLds<TY, ZC>& sm, const BlockGrid& g, int xcd,
+                                            BlockLds<TW, TY, ZC>& sm, const BlockGrid& g, int xcd,
                                             int at) {
   int tx, ty, zl;
   if (!block_at(g, xcd, at, &tx, &ty, &zl)) return;
   constexpr bool damp = LM != 0;
   const ChunkInfo c = chunk_of(zl, a.nz, a.w, ZC, damp);
   BlockAt b;
-  b.x0 = tx * kTX;
+  b.x0 = tx * TW;
   b.y0 = ty * TY;
   b.zb = c.zb;
   b.nzb = c.ze - c.zb;
-  const int x = b.x0 + (threadIdx.x & 63);
-  const int y = b.y0 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int x = b.x0 + (int)(threadIdx.x & (TW - 1));
+  const int y = b.y0 + (TW == 64 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)
+                                 : (int)threadIdx.x / TW);
   const bool lay = damp && x < a.nx && y < a.ny &&
                    (c.cap || x < a.w || x >= a.nx - a.w || y < a.w || y >= a.ny - a.w);
   const bool none = LM == 0 || !__any(lay);
   if (b.nzb == ZC) {
     if (none)
-      block_rows<S, TY, ZC, 0, true, NTP>(a, io, sm, b, false);
+      block_rows<S, TW, TY, ZC, 0, true, NTP>(a, io, sm, b, false);
     else if (LM == 2 && !c.cap)
-      block_rows<S, TY, ZC, 3, true, NTP>(a, io, sm, b, lay);
+      block_rows<S, TW, TY, ZC, 3, true, NTP>(a, io, sm, b, lay);
     else
-      block_rows<S, TY, ZC, LM, true, NTP>(a, io, sm, b, lay);
+      block_rows<S, TW, TY, ZC, LM, true, NTP>(a, io, sm, b, lay);
   } else {
     if (none)
-      block_rows<S, TY, ZC, 0, false, NTP>(a, io, sm, b, false);
+      block_rows<S, TW, TY, ZC, 0, false, NTP>(a, io, sm, b, false);
     else
-      block_rows<S, TY, ZC, LM, false, NTP>(a, io, sm, b, lay);
+      block_rows<S, TW, TY, ZC, LM, false, NTP>(a, io, sm, b, lay);
   }
 }
 
@@ -644,26 +651,31 @@ __global__ __launch_bounds__(256, 4) void k_sweep_duo(SweepArgs a, StepIO io, Bl
   duo_sweep<S, LM>(a, io, sm, g, blockIdx.x & 7, (a.step & 1) ? g.per_xcd - 1 - slot : slot);
 }
 
-template <class S, int TY, int ZC, int LM, bool NTP>
-__global__ __launch_bounds__(64 * TY, 4) void k_sweep_block(SweepArgs a, StepIO io, BlockGrid g) {
-  __shared__ BlockLds<TY, ZC> sm;
+template <class S, int TW, int TY, int ZC, int LM, bool NTP>
+__global__ __launch_bounds__(TW * TY, 4) void k_sweep_block(SweepArgs a, StepIO io, BlockGrid g) {
+  __shared__ BlockLds<TW, TY, ZC> sm;
   const int slot = blockIdx.x >> 3;
   if (slot >= g.per_xcd) {  // receivers of u^n, the last step's field
-    record_row<S>(a, io, (blockIdx.x - 8 * g.per_xcd) * 64 * TY + threadIdx.x);
+    record_row<S>(a, io, (blockIdx.x - 8 * g.per_xcd) * TW * TY + threadIdx.x);
     return;
   }
   // Odd steps walk the blocks backwards: what a step touched last is still in
   // the memory-side cache when the next one starts (256^3: 60.7 -> 51.6 us).
-  block_sweep<S, TY, ZC, LM, NTP>(a, io, sm, g, blockIdx.x & 7,
-                                  (a.step & 1) ? g.per_xcd - 1 - slot : slot);
+  block_sweep<S, TW, TY, ZC, LM, NTP>(a, io, sm, g, blockIdx.x & 7,
+                                      (a.step & 1) ? g.per_xcd - 1 - slot : slot);
 }
+
+union WideOrNarrow {
+  BlockLds<64, 4, 4> wide;
+  BlockLds<32, 8, 4> narrow;
+};
 
 // Several members of a batch in one launch.  The sweep's arguments come from
 // the batch's table, everything that changes from step to step by value.
 template <class S, int LM, bool DUO>
 __global__ __launch_bounds__(256, 4) void k_sweep_block_batch(const BatchShot* __restrict__ shots,
                                                               BlockBatch bb) {
-  __shared__ __attribute__((aligned(16))) std::conditional_t<DUO, DuoLds, BlockLds<4, 4>> sm;
+  __shared__ __attribute__((aligned(16))) std::conditional_t<DUO, DuoLds, WideOrNarrow> sm;
   const int bid = (int)order_block(blockIdx.x, gridDim.x, bb.back);
   int m = 0;
   for (int i = 1; i < bb.n; ++i)
@@ -680,8 +692,10 @@ __global__ __launch_bounds__(256, 4) void k_sweep_block_batch(const BatchShot* _
   }
   if constexpr (DUO)
     duo_sweep<S, LM>(a, e.io, sm, e.g, local & 7, local >> 3);
+  else if (e.g.narrow)
+    block_sweep<S, 32, 8, 4, LM, false>(a, e.io, sm.narrow, e.g, local & 7, local >> 3);
   else
-    block_sweep<S, 4, 4, LM, false>(a, e.io, sm, e.g, local & 7, local >> 3);
+    block_sweep<S, 64, 4, 4, LM, false>(a, e.io, sm.wide, e.g, local & 7, local >> 3);
 }
 
 template <class S>
@@ -693,9 +707,21 @@ __global__ __launch_bounds__(256) void k_record_members(const BatchShot* __restr
   record_row<S>(a, e.io, blockIdx.x * 256 + threadIdx.x);
 }
 
+// 4 x 4 blocks are 64 points wide, or 32 x 8 where that saves a sixth of the lanes
+// or more: with 3 or 5 tiles of 32 columns (65..96 and 129..160 points in x) 64-wide
+// tiles leave a half tile idle.  us per step, 64 -> 32 wide: 70x45x37 5.05 -> 4.85,
+// 96^3 7.05 -> 6.6 (no layer 5.9 -> 5.3), 160^3 16.8 -> 15.6 (no layer 12.8 -> 11.3),
+// 160^3 in f16 16.7 -> 14.3 and stochastic bf16 18.0 -> 16.4.  With 7 tiles the
+// saving no longer decides (224^3 37.4..39.9 -> 38.3..39.4), and where it saves none,
+// 32-wide tiles read more x halo (176x144x160 16.6 -> 17.5, 256^3 55 -> 56.4).
+bool narrow_blocks(const SweepArgs& a) {
+  const int tiles = cdiv(a.nx, 32);
+  return tiles == 3 || tiles == 5;
+}
+
 // false: the grid does not fit the index arithmetic.
-bool block_grid(const SweepArgs& a, int ty, int zc, BlockGrid* g) {
-  g->tiles_x = cdiv(a.nx, kTX);
+bool block_grid(const SweepArgs& a, int tw, int ty, int zc, BlockGrid* g) {
+  g->tiles_x = cdiv(a.nx, tw);
   g->tiles_y = cdiv(a.ny, ty);
   g->slab = cdiv(g->tiles_y, 8);
   const int layers = chunk_count(a.nz, a.w, zc, a.damping != 0);
@@ -708,23 +734,28 @@ bool block_grid(const SweepArgs& a, int ty, int zc, BlockGrid* g) {
   auto magic = [](int d) { return (uint32_t)(0xffffffffu / (uint32_t)d + 1u); };
   g->mx = magic(g->tiles_x);
   g->mslab = magic(g->slab);
+  g->narrow = tw == 32;
   return true;
 }
 
-template <class S, int TY, int ZC, int LM, bool NTP>
+bool block_grid_44(const SweepArgs& a, BlockGrid* g) {
+  return narrow_blocks(a) ? block_grid(a, 32, 8, 4, g) : block_grid(a, kTX, 4, 4, g);
+}
+
+template <class S, int TW, int TY, int ZC, int LM, bool NTP>
 hipError_t block_t(const SweepArgs& a, const StepIO& io, hipStream_t st) {
   BlockGrid g;
-  if (!block_grid(a, TY, ZC, &g)) return hipErrorInvalidValue;
-  const int rec = io.nrec > 0 ? cdiv(io.nrec, 64 * TY) : 0;
-  const dim3 grid((unsigned)(8 * g.per_xcd + rec)), blk(64 * TY);
-  hipLaunchKernelGGL((k_sweep_block<S, TY, ZC, LM, NTP>), grid, blk, 0, st, a, io, g);
+  if (!block_grid(a, TW, TY, ZC, &g)) return hipErrorInvalidValue;
+  const int rec = io.nrec > 0 ? cdiv(io.nrec, TW * TY) : 0;
+  const dim3 grid((unsigned)(8 * g.per_xcd + rec)), blk(TW * TY);
+  hipLaunchKernelGGL((k_sweep_block<S, TW, TY, ZC, LM, NTP>), grid, blk, 0, st, a, io, g);
   return hipGetLastError();
 }
 
 template <class S, int LM>
 hipError_t duo_t(const SweepArgs& a, const StepIO& io, hipStream_t st) {
   BlockGrid g;
-  if (!block_grid(a, kDY, kDZ, &g)) return hipErrorInvalidValue;
+  if (!block_grid(a, kTX, kDY, kDZ, &g)) return hipErrorInvalidValue;
   const int rec = io.nrec > 0 ? cdiv(io.nrec, 256) : 0;
   hipLaunchKernelGGL((k_sweep_duo<S, LM>), dim3((unsigned)(8 * g.per_xcd + rec)), dim3(256), 0, st, a, io, g);
   return hipGetLastError();
@@ -732,16 +763,21 @@ hipError_t duo_t(const SweepArgs& a, const StepIO& io, hipStream_t st) {
 
 template <class S>
 hipError_t block_s(const SweepArgs& a, const StepIO& io, int ty, int zc, bool nt, hipStream_t st) {
-  if (ty == 4 && zc == 4)
-    return a.eta       ? block_t<S, 4, 4, 1, false>(a, io, st)
-           : a.damping ? block_t<S, 4, 4, 2, false>(a, io, st)
-                       : block_t<S, 4, 4, 0, false>(a, io, st);
+  if (ty == 4 && zc == 4) {
+    if (narrow_blocks(a))
+      return a.eta       ? block_t<S, 32, 8, 4, 1, false>(a, io, st)
+             : a.damping ? block_t<S, 32, 8, 4, 2, false>(a, io, st)
+                         : block_t<S, 32, 8, 4, 0, false>(a, io, st);
+    return a.eta       ? block_t<S, 64, 4, 4, 1, false>(a, io, st)
+           : a.damping ? block_t<S, 64, 4, 4, 2, false>(a, io, st)
+                       : block_t<S, 64, 4, 4, 0, false>(a, io, st);
+  }
   if constexpr (sizeof(typename S::T) == 2 && !S::kSR) {
     if (ty == kDY && zc == kDZ && !a.eta) return a.damping ? duo_t<S, 2>(a, io, st) : duo_t<S, 0>(a, io, st);
   }
   if constexpr (!S::kSR) {
     if (ty == 8 && zc == 8 && !a.damping)
-      return nt ? block_t<S, 8, 8, 0, true>(a, io, st) : block_t<S, 8, 8, 0, false>(a, io, st);
+      return nt ? block_t<S, 64, 8, 8, 0, true>(a, io, st) : block_t<S, 64, 8, 8, 0, false>(a, io, st);
   }
   return hipErrorInvalidValue;
 }
@@ -749,9 +785,11 @@ hipError_t block_s(const SweepArgs& a, const StepIO& io, int ty, int zc, bool nt
 }  // namespace
 
 bool block_config_supported(int ty, int zc, const SweepArgs& a, int storage) {
-  const bool cfg = (ty == 4 && zc == 4) || (ty == kDY && zc == kDZ && !a.eta && (storage == 1 || storage == 2)) || (ty == 8 && zc == 8 && !a.damping && storage != 3);
+  const bool cfg = (ty == 4 && zc == 4) ||
+                   (ty == kDY && zc == kDZ && !a.eta && (storage == 1 || storage == 2)) ||
+                   (ty == 8 && zc == 8 && !a.damping && storage != 3);
   BlockGrid g;
-  return cfg && block_grid(a, ty, zc, &g);
+  return cfg && (ty == 4 ? block_grid_44(a, &g) : block_grid(a, kTX, ty, zc, &g));
 }
 
 int64_t sweep_footprint(int nx, int ny, int nz, int w, bool damping, bool eta_array, int es) {
@@ -796,7 +834,7 @@ hipError_t launch_sweep_block(const SweepArgs& a, const StepIO& io, int storage,
 }
 
 int block_batch_grid(const SweepArgs& a, bool duo, int nrec, BlockGrid* g) {
-  if (!block_grid(a, duo ? kDY : 4, duo ? kDZ : 4, g)) return 0;
+  if (!(duo ? block_grid(a, kTX, kDY, kDZ, g) : block_grid_44(a, g))) return 0;
   return 8 * (g->per_xcd + cdiv(cdiv(nrec, 256), 8));
 }
 

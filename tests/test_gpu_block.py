@@ -188,3 +188,20 @@ def test_batch_by_size_equals_solo(W, members, graph):
     for i, sh in enumerate(shots):
         for x, y in zip(_state(W, sh), _solo(W, members[i], n[i])):
             assert x.shape == y.shape and np.array_equal(x, y), (i, members[i])
+
+
+@pytest.mark.parametrize("nx", [64, 65, 96, 97, 128, 129, 160, 161])
+@pytest.mark.parametrize("storage", ["f32", "bf16", "f16", "bf16sr"])
+def test_block_tile_widths(W, nx, storage):
+    """Either side of each change between 64 and 32 columns per block, with
+    sources one above the other in both rows of a 32-wide wavefront and in the
+    first and last column."""
+    ny, nz, w, steps = 27, 15, 4, 5
+    shot = synth.config_small_layered(nx, ny, nz, w, steps, seed=nx, nsrc=4)
+    for s, p in enumerate(((nx - 1, 12, 7), (nx - 1, 13, 7), (31, 13, 7), (0, 26, 14))):
+        shot.src[s] = p
+    expect = oracle.run_shot(shot, steps=steps, precision="f32", storage=storage)
+    say(f"case block width {nx} {storage}")
+    got = run(W, shot, (2, 3), (10, 1, 4, 4), storage.replace("sr", ""), sr=storage == "bf16sr")
+    for key in ("u", "u_prev", "phi", "traces"):
+        assert np.array_equal(got[key], expect[key]), (nx, storage, key)
