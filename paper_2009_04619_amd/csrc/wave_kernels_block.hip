@@ -18,7 +18,7 @@
 // the receivers of the step before, which saves the second launch.
 //
 // us per step with a source and a receiver line, before (64 x 8 streaming
-// tiles) -> now: 64^3 22.5 -> 4.5, 128^3 23.4 -> 9.7, 160^3 29.5 -> 16.6, 192^3 35.9
+// tiles) -> now: 64^3 22.5 -> 4.1, 128^3 23.4 -> 9.2, 160^3 29.5 -> 15, 192^3 35.9
 // -> 24, 256^3 65.0 -> 55 (20-cell layer; 16 at 64^3); 256^3 without a layer 50.1
 // -> 40 (7.2 TB/s of its algorithmic bytes on a zero field; a copy inside that
 // cache moves 8.3).  bf16 with two points per lane: 128^3 23.5 -> 8.2, 256^3 57 ->
@@ -652,9 +652,19 @@ __device__ __forceinline__ void duo_sweep(const SweepArgs& a, const StepIO& io, 
   }
 }
 
+// Requests every 64-byte line of the kernel's arguments at its start, in one wait.
+// Each step's arguments are new to the scalar cache; read where they are first
+// used, their lines arrive one after the other, which a small grid has nothing to
+// hide behind.  us per step: 64^3 4.5 -> 4.1, 70x45x37 4.85 -> 4.35, 96^3 6.6 ->
+// 6.0, 128^3 9.8 -> 9.2, 176x144x160 16.8 -> 16.3; from 256^3 on no difference.
+__device__ __forceinline__ void touch_args(const SweepArgs& a, const StepIO& io, const BlockGrid& g) {
+  asm volatile("" ::"s"(a.nx), "s"(a.etab), "s"(io.sz[3]), "s"(g.per_xcd), "s"(a.step));
+}
+
 template <class S, int LM>
 __global__ __launch_bounds__(256, 4) void k_sweep_duo(SweepArgs a, StepIO io, BlockGrid g) {
   __shared__ __attribute__((aligned(16))) DuoLds sm;
+  touch_args(a, io, g);
   const int slot = blockIdx.x >> 3;
   if (slot >= g.per_xcd) {
     record_row<S>(a, io, (blockIdx.x - 8 * g.per_xcd) * 256 + threadIdx.x);
@@ -666,6 +676,7 @@ __global__ __launch_bounds__(256, 4) void k_sweep_duo(SweepArgs a, StepIO io, Bl
 template <class S, int TW, int TY, int ZC, int LM, bool NTP>
 __global__ __launch_bounds__(TW * TY, 4) void k_sweep_block(SweepArgs a, StepIO io, BlockGrid g) {
   __shared__ BlockLds<TW, TY, ZC> sm;
+  touch_args(a, io, g);
   const int slot = blockIdx.x >> 3;
   if (slot >= g.per_xcd) {  // receivers of u^n, the last step's field
     record_row<S>(a, io, (blockIdx.x - 8 * g.per_xcd) * TW * TY + threadIdx.x);
