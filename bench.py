@@ -40,11 +40,11 @@ KERNELS = {0: ("k_sweep_direct", "direct", ("wave_kernels.hip", "wave_direct.h",
            3: ("k_sweep_gmem", "gmem", ("wave_shapes.hip", "wave_direct.h", "wave_point.h")),
            4: ("k_sweep_ring", "ring", ("wave_shapes.hip", "wave_direct.h", "wave_point.h")),
            5: ("k_sweep_shift", "shift", ("wave_shapes.hip", "wave_direct.h", "wave_point.h")),
-           6: ("k_sweep_pair", "pair", ("wave_kernels_pair.hip", "wave_point.h")),
+           6: ("k_sweep_pair", "pair", ("wave_kernels_pair.hip", "wave_pair.h", "wave_point.h")),
            7: ("k_sweep_stream", "semi", ("wave_kernels.hip", "wave_point.h")),
            8: ("k_sweep_persist", "persist", ("wave_kernels.hip", "wave_point.h")),
            9: ("k_sweep_stream", "shuffle", ("wave_kernels.hip", "wave_point.h")),
-           10: ("k_sweep_block", "block", ("wave_kernels_block.hip", "wave_point.h"))}
+           10: ("k_sweep_block", "block", ("wave_kernels_block.hip", "wave_pair.h", "wave_point.h"))}
 
 
 def kernel_source_sha(variant: int = 1) -> str:

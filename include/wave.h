@@ -333,7 +333,9 @@ int wave_energy_noalloc(wave_ctx *ctx, double *dev_out);
                                 workgroup, every operand of the block
                                 requested at once, up to 4 sources and the
                                 receivers in the same launch; rows_per_wave =
-                                1, (waves_per_group, zchunk) = (ty, zc): (4,4);
+                                1, (waves_per_group, zchunk) = (ty, zc): (4,4),
+                                run as 32 x 8 x 4 points where 64-wide blocks
+                                leave half a tile idle (3 or 5 tiles of 32);
                                 (8,4), two points per lane, with 16-bit storage,
                                 no eta array and no stochastic rounding; (8,8)
                                 with damping off and no stochastic rounding;
@@ -346,13 +348,13 @@ int wave_energy_noalloc(wave_ctx *ctx, double *dev_out);
  * {(1,16), (1,8), (2,8), (2,4)}, and (2,16) (64 x 32 tiles) without an eta
  * array.  The default is WAVE_KERNEL_BLOCK where the state (u^n, u^{n-1}, vp,
  * phi and eta of the points that have them) is at most 280 MB (360 MB with two
- * points per lane), and with damping off on larger grids too; else, with 16-bit storage and no eta array,
- * WAVE_KERNEL_PAIR with 8 rows (with stochastic rounding 16 rows, and only on
- * the large grids of the next clause); else WAVE_KERNEL_PERSIST with (1,16)
- * tiles and its automatic chunk (half the streaming kernel's) on grids large
- * enough for 64-plane chunks of 64 x 16 tiles with about 2048 workgroups
- * (512^3 and up for cubes), else WAVE_KERNEL_STREAM with (1,8) tiles (also
- * where the CU count cannot be queried).  The streaming
+ * points per lane), and with damping off on larger grids too; else, with 16-bit
+ * storage and no eta array, WAVE_KERNEL_PAIR with 8 rows (with stochastic
+ * rounding 16 rows, and only on the large grids of the next clause); else
+ * WAVE_KERNEL_PERSIST with (1,16) tiles and its automatic chunk (half the
+ * streaming kernel's) on grids large enough for 64-plane chunks of 64 x 16 tiles
+ * with about 2048 workgroups (512^3 and up for cubes), else WAVE_KERNEL_STREAM
+ * with (1,8) tiles (also where the CU count cannot be queried).  The streaming
  * kernel addresses a chunk's planes with 32-bit offsets, so zchunk is cut
  * to what keeps zchunk + 8 float planes below 2 GiB; a grid whose single
  * plane is too large for that runs the direct kernel.  With
@@ -367,10 +369,10 @@ int wave_set_kernel(wave_ctx *ctx, int32_t variant, int32_t rows_per_wave,
 /* Autotuner: advance the simulation by one untimed and `trial_steps` timed
  * real steps under the persistent launch (16 and 8 rows, two z-chunk
  * lengths; the first of them gives its place to the block kernel where that is
- * the default and WAVE_TWO_STEP is not set), each compiled streaming tile shape at a few z-chunk lengths,
- * with WAVE_TWO_STEP the two-step kernel with a few z-chunk lengths
- * (trial_steps rounded up to even there), the two-points-per-lane kernel
- * (both tile heights, two z-chunk lengths; not with an eta array), the
+ * the default and WAVE_TWO_STEP is not set), each compiled streaming tile shape
+ * at a few z-chunk lengths, with WAVE_TWO_STEP the two-step kernel with a few
+ * z-chunk lengths (trial_steps rounded up to even there), the two-points-per-lane
+ * kernel (both tile heights, two z-chunk lengths; not with an eta array), the
  * shuffle kernel (both tile heights), then four of the paper's other code
  * shapes (WAVE_KERNEL_GMEM 8x8x8 and 64x4x4, RING and SHIFT with 16 rows);
  * never WAVE_KERNEL_SEMI, which rounds differently.  Every candidate computes
@@ -477,9 +479,10 @@ int wave_batch_set_kernel(wave_batch *b, int32_t rows_per_wave, int32_t waves_pe
 int wave_batch_set_graph(wave_batch *b, int32_t steps_per_graph);
 
 /* Autotuner for a batch: runs trial_steps steps without a set tile and under
- * each compiled tile shape but 64 x 8 in four wavefronts (and the two-points-per-lane tiles when no member holds an eta
- * array) and keeps the fastest; *chosen = {rows_per_wave, waves_per_group}
- * as wave_batch_set_kernel takes them. */
+ * each compiled tile shape but 64 x 8 in four wavefronts (and the
+ * two-points-per-lane tiles when no member holds an eta array) and keeps the
+ * fastest; *chosen = {rows_per_wave, waves_per_group} as wave_batch_set_kernel
+ * takes them. */
 int wave_batch_tune(wave_batch *b, int32_t trial_steps, int32_t chosen[2]);
 
 /* Wait for the batch's work, release it (members stay valid contexts). */
