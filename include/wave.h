@@ -346,9 +346,10 @@ int wave_energy_noalloc(wave_ctx *ctx, double *dev_out);
  * z planes one workgroup streams (0 = automatic).  Only compiled
  * combinations are accepted (EINVAL otherwise): (RY, NW) in
  * {(1,16), (1,8), (2,8), (2,4)}, and (2,16) (64 x 32 tiles) without an eta
- * array.  The default is WAVE_KERNEL_BLOCK where the state (u^n, u^{n-1}, vp,
- * phi and eta of the points that have them) is at most 280 MB (360 MB with two
- * points per lane), and with damping off on larger grids too; else, with 16-bit
+ * array.  The default is WAVE_KERNEL_BLOCK without WAVE_TWO_STEP where the
+ * state (u^n, u^{n-1}, vp, phi and eta of the points that have them) is at most
+ * 280 MB (360 MB with two points per lane), and with damping off and no stochastic
+ * rounding on larger grids too; else, with 16-bit
  * storage and no eta array, WAVE_KERNEL_PAIR with 8 rows (with stochastic
  * rounding 16 rows, and only on the large grids of the next clause); else
  * WAVE_KERNEL_PERSIST with (1,16) tiles and its automatic chunk (half the
@@ -367,9 +368,9 @@ int wave_set_kernel(wave_ctx *ctx, int32_t variant, int32_t rows_per_wave,
                     int32_t waves_per_group, int32_t zchunk);
 
 /* Autotuner: advance the simulation by one untimed and `trial_steps` timed
- * real steps under the persistent launch (16 and 8 rows, two z-chunk
- * lengths; the first of them gives its place to the block kernel where that is
- * the default and WAVE_TWO_STEP is not set), each compiled streaming tile shape
+ * real steps under the block kernel where that is the default, the persistent
+ * launch (16 and 8 rows, two z-chunk lengths; without the first of them where the
+ * trace buffer lacks the room), each compiled streaming tile shape
  * at a few z-chunk lengths, with WAVE_TWO_STEP the two-step kernel with a few
  * z-chunk lengths (trial_steps rounded up to even there), the two-points-per-lane
  * kernel (both tile heights, two z-chunk lengths; not with an eta array), the

@@ -695,6 +695,14 @@ int pair_zchunk(const wave_ctx* c, int ty, int zchunk, int semi_nw = 0) {
   return std::min(zc, lim);
 }
 
+// The block a context's default launch uses, or 0, 0.  Contexts set up for two
+// steps per launch keep the streaming kernels, which are what wave_tune compares
+// with that kernel.
+void block_default_of(const wave_ctx* c, int* ty, int* zc) {
+  *ty = *zc = 0;
+  if (!two_step(&c->d)) wave::block_default(sweep_args(c), kernel_storage(&c->d), ty, zc);
+}
+
 // State of a member that its sweep touches, and what a group of several members
 // may hold to stay in the 256 MB memory-side cache between steps (8 float32
 // shots of 128-256 cells, 46-145 MB each, us per step at 100, 150, 200, 240,
@@ -1070,7 +1078,7 @@ int wave_alloc(const wave_desc* d, const float* vel, const float* eta, void* dev
   c->zchunk = 0;
   {
     int bty, bzc;
-    wave::block_default(sweep_args(c), kernel_storage(d), &bty, &bzc);
+    block_default_of(c, &bty, &bzc);
     // 16-bit storage moves half the bytes per instruction of a lane, so on
     // grids past the block kernel's it runs two points per lane: 128 x 8 tiles
     // (bf16, us per sweep, against the best one-point launch: 384^3 134 / 147,
@@ -1651,9 +1659,14 @@ int wave_tune(wave_ctx* c, int32_t trial_steps, int32_t chosen[4]) {
     if (std::find(cand.begin(), cand.end(), e) == cand.end()) cand.push_back(e);
   };
   const bool ea = eta_array(&c->d);
-  // the persistent launch first, at its automatic chunk and twice that; where
-  // the block kernel is the default it takes the first of these places
-  // (not with WAVE_TWO_STEP, whose tuning compares the streaming shapes)
+  // the default first where it is the block kernel, then the persistent launch
+  // at its automatic chunk and twice that
+  {
+    int bty, bzc;
+    block_default_of(c, &bty, &bzc);
+    if (bty) add({WAVE_KERNEL_BLOCK, 1, bty, bzc});
+  }
+  const size_t after_block = cand.size();
   for (const auto& t : {std::array<int, 2>{1, 16}, std::array<int, 2>{1, 8}}) {
     if (c->groups < 8) continue;
     const int za = persist_zchunk(c, t[0], t[1], 0);
@@ -1661,11 +1674,6 @@ int wave_tune(wave_ctx* c, int32_t trial_steps, int32_t chosen[4]) {
       const int zc = stream_zchunk(c, t[0], t[1], z);
       if (zc >= 1) add({WAVE_KERNEL_PERSIST, t[0], t[1], zc});
     }
-  }
-  {
-    int bty, bzc;
-    wave::block_default(sweep_args(c), kernel_storage(&c->d), &bty, &bzc);
-    if (bty && !cand.empty() && !two_step(&c->d)) cand[0] = {WAVE_KERNEL_BLOCK, 1, bty, bzc};
   }
   for (int k = 0; k < nshape; ++k) {
     const int ry = kShapes[k][0], nw = kShapes[k][1];
@@ -1715,8 +1723,16 @@ int wave_tune(wave_ctx* c, int32_t trial_steps, int32_t chosen[4]) {
   // each candidate first takes one untimed step (the first launch after a
   // kernel switch runs cold), then its timed trial
   for (const auto& e : cand) total += 1 + (e[0] == WAVE_KERNEL_STREAM2 ? trial2 : trial_steps);
-  if (c->nrec > 0 && (int64_t)c->trace_count + total > c->d.max_steps)
-    return fail(WAVE_EINVAL, "tuning steps would overflow the trace buffer");
+  auto traces_fit = [&]() { return c->nrec == 0 || (int64_t)c->trace_count + total <= c->d.max_steps; };
+  // where the trace buffer has no room for one more trial, the block kernel
+  // takes the place of the first persistent launch, which was slower on every grid
+  // measured that runs blocks by default (160^3 44.9 us against 15; 512^3 without
+  // a layer 386 against 362)
+  if (!traces_fit() && after_block == 1 && cand.size() > 1 && cand[1][0] == WAVE_KERNEL_PERSIST) {
+    cand.erase(cand.begin() + 1);
+    total -= 1 + trial_steps;
+  }
+  if (!traces_fit()) return fail(WAVE_EINVAL, "tuning steps would overflow the trace buffer");
   if (c->step + total > 0x7fffffff) return fail(WAVE_EINVAL, "step counter overflow");
   hipEvent_t e0, e1;
   HIPCHK(c, hipEventCreate(&e0), "hipEventCreate");

@@ -1,0 +1,82 @@
+"""What the tuners settle on: never a launch slower than the one a context or a
+batch starts with.  Times are the least of several runs of each side in turn; the
+margins are several times the 1-3 % that such runs differ by, and a fraction of
+what the faults they guard against cost."""
+import sys
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def W():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU (run with -m 'not gpu' on CPU)")
+    from paper_2009_04619_amd import wave
+    return wave
+
+
+def say(*a):
+    print(*a, flush=True)
+    sys.stdout.flush()
+
+
+def shot(W, nx, ny, nz, w, max_steps, storage="f32", **kw):
+    rng = np.random.default_rng(nx + ny + nz)
+    vel = np.resize(rng.uniform(1500.0, 4000.0, 4093).astype(np.float32), (nz, ny, nx))
+    sh = W.Shot(nx, ny, nz, w, 10.0, 10.0, 10.0, 9e-4, vel, storage=storage, max_src=1, max_rec=8,
+                max_steps=max_steps, **kw)
+    sh.inject(nx // 2, ny // 2, nz // 2, np.ones(8, np.float32))
+    sh.record(np.array([[i * nx // 8, ny // 2, nz // 2] for i in range(8)], np.int32))
+    u = np.resize(0.1 * rng.standard_normal(65537).astype(np.float32), (nz, ny, nx))
+    sh.write(W.WAVE_FIELD_U, u)
+    sh.write(W.WAVE_FIELD_UPREV, u)
+    return sh
+
+
+def least_us(things, n, reps=6):
+    """Microseconds per step of each (run, stream) pair, taken in turn."""
+    import torch
+    best = [np.inf] * len(things)
+    e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+    for _ in range(reps):
+        for q, (run, stream) in enumerate(things):
+            run(2)
+            e0.record(stream)
+            run(n)
+            e1.record(stream)
+            e1.synchronize()
+            best[q] = min(best[q], e0.elapsed_time(e1) / n * 1e3)
+    return best
+
+
+@pytest.mark.parametrize("kw", [dict(), dict(two_step=True), dict(storage="bf16"),
+                                dict(storage="bf16", two_step=True)], ids=str)
+def test_tuning_a_shot_keeps_its_speed(W, kw):
+    say(f"case tuned shot {kw}")
+    shots = [shot(W, 64, 64, 64, 16, 1200, **kw) for _ in range(2)]
+    cfg = shots[1].tune(4)
+    untuned, tuned = least_us([(sh.step, sh.stream) for sh in shots], 100)
+    say(f"untuned {untuned:.2f}, tuned {tuned:.2f} us a step {tuple(cfg)}")
+    for sh in shots:
+        sh.close()
+    assert tuned < 1.25 * untuned, (kw, cfg, tuned, untuned)
+
+
+def test_tuning_fits_the_trace_buffer_it_fitted_before(W):
+    """The block kernel's trial is dropped against the first persistent one where
+    the trace buffer has no room for both: 70 x 45 x 37 takes as many steps as the
+    candidates without the block kernel need."""
+    say("case tuner and trace room")
+    sh = shot(W, 70, 45, 37, 5, 400)
+    sh.tune(2)
+    full = sh.step_count
+    sh.close()
+    for room, ok in ((full, True), (full - 1, True), (full - 3, True), (full - 4, False)):
+        sh = shot(W, 70, 45, 37, 5, room)
+        rc, _ = W.wave_tune(sh.ctx, 2)
+        assert (rc == W.WAVE_OK) == ok, (room, full)
+        sh.close()
