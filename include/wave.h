@@ -346,10 +346,10 @@ int wave_energy_noalloc(wave_ctx *ctx, double *dev_out);
  * z planes one workgroup streams (0 = automatic).  Only compiled
  * combinations are accepted (EINVAL otherwise): (RY, NW) in
  * {(1,16), (1,8), (2,8), (2,4)}, and (2,16) (64 x 32 tiles) without an eta
- * array.  The default is WAVE_KERNEL_BLOCK without WAVE_TWO_STEP where the
- * state (u^n, u^{n-1}, vp, phi and eta of the points that have them) is at most
- * 280 MB (360 MB with two points per lane), and with damping off and no stochastic
- * rounding on larger grids too; else, with 16-bit
+ * array.  The default is WAVE_KERNEL_BLOCK where the state (u^n, u^{n-1}, vp,
+ * phi and eta of the points that have them) is at most 280 MB (360 MB with two
+ * points per lane), and with damping off and no stochastic rounding on larger
+ * grids too; else, with 16-bit
  * storage and no eta array, WAVE_KERNEL_PAIR with 8 rows (with stochastic
  * rounding 16 rows, and only on the large grids of the next clause); else
  * WAVE_KERNEL_PERSIST with (1,16) tiles and its automatic chunk (half the
@@ -383,7 +383,9 @@ int wave_set_kernel(wave_ctx *ctx, int32_t variant, int32_t rows_per_wave,
  * near-ties pick stably).  *chosen (may be NULL) receives the
  * wave_set_kernel arguments {variant, rows_per_wave, waves_per_group,
  * zchunk} of the pick; {0, 0, 0, 0} when the planes are too large to stream
- * and the direct kernel is kept.  Synchronises.  EINVAL if the steps would
+ * and the direct kernel is kept.  With WAVE_TWO_STEP, where the block kernel is
+ * the default and beats every other launch, it stays in force and *chosen
+ * names the fastest of the others.  Synchronises.  EINVAL if the steps would
  * overflow the trace buffer. */
 int wave_tune(wave_ctx *ctx, int32_t trial_steps, int32_t chosen[4]);
 
