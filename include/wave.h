@@ -481,11 +481,13 @@ int wave_batch_remaining(const wave_batch *b, const wave_ctx *ctx, int32_t *rema
 int wave_batch_set_kernel(wave_batch *b, int32_t rows_per_wave, int32_t waves_per_group);
 int wave_batch_set_graph(wave_batch *b, int32_t steps_per_graph);
 
-/* Autotuner for a batch: runs trial_steps steps without a set tile and under
- * each compiled tile shape but 64 x 8 in four wavefronts (and the
- * two-points-per-lane tiles when no member holds an eta array) and keeps the
- * fastest; *chosen = {rows_per_wave, waves_per_group} as wave_batch_set_kernel
- * takes them. */
+/* Autotuner for a batch: runs of 1, 1 and 1 + trial_steps steps under each
+ * compiled tile shape (and the two-points-per-lane tiles when no member holds an
+ * eta array) and of 4, 1, 4 and 4 + max(8, trial_steps) steps without a set tile,
+ * all plain launches.  Keeps the one whose later steps cost the least per point;
+ * no tile is set where the members run out of steps before all are timed.
+ * *chosen = {rows_per_wave, waves_per_group} as wave_batch_set_kernel takes them.
+ * Synchronises. */
 int wave_batch_tune(wave_batch *b, int32_t trial_steps, int32_t chosen[2]);
 
 /* Wait for the batch's work, release it (members stay valid contexts). */

@@ -592,9 +592,6 @@ struct wave_batch {
   };
   std::vector<Graph> graphs;
   bool broken;
-  // while the tuner times a run: three events for each block group of more than
-  // one step (its start, after its first step, its end)
-  std::vector<hipEvent_t>* marks = nullptr;
 };
 
 // Members first .. first + count - 1 of a batch take all their steps of a run
@@ -883,20 +880,8 @@ hipError_t batch_run_block(wave_batch* b, const wave_batch::Group& g) {
     step_samples(c, c->step + t, &m.io);
     step_receivers(c, t > 0, c->trace_count + t - 1, &m.io);
   };
-  auto mark = [&]() -> hipError_t {
-    if (!b->marks || h[0].target < 2) return hipSuccess;
-    hipEvent_t ev;
-    hipError_t e = hipEventCreate(&ev);
-    if (e != hipSuccess) return e;
-    b->marks->push_back(ev);
-    return hipEventRecord(ev, b->stream);
-  };
   int k = g.count;
   for (int32_t t = 0; t < h[0].target; ++t) {
-    if (t < 2) {
-      const hipError_t e = mark();
-      if (e != hipSuccess) return e;
-    }
     while (h[k - 1].target <= t) --k;
     for (int i = 0; i < k; ++i) at_step(i, t);
     bb.n = k;
@@ -914,8 +899,6 @@ hipError_t batch_run_block(wave_batch* b, const wave_batch::Group& g) {
     }
     if (e != hipSuccess) return e;
   }
-  const hipError_t em = mark();
-  if (em != hipSuccess) return em;
   for (int i = 0; i < g.count; ++i) at_step(i, h[i].target);
   bb.n = g.count;
   return wave::launch_record_members(b->d_shots + g.first, bb, b->kstore, b->stream);
@@ -2124,73 +2107,92 @@ int wave_batch_tune(wave_batch* b, int32_t trial_steps, int32_t chosen[2]) {
   CHECK_BATCH(b);
   if (trial_steps < 1) return fail(WAVE_EINVAL, "trial_steps < 1");
   const int nshape = (int)(sizeof(kShapes) / sizeof(kShapes[0]));
-  float best = 0.0f;
-  int pr = 4, pn = 4;
-  // each member by its size (in the place of the 64 x 8 tile of four
-  // wavefronts), the compiled one-point tiles, then two points per lane (128 x
-  // 16, 128 x 8) when no member holds an eta array
+  // the compiled one-point tiles, two points per lane (128 x 16, 128 x 8) when no
+  // member holds an eta array, then each member by its size
   std::vector<std::array<int, 2>> shapes;
   bool pair_ok = true;
   for (wave_ctx* c : b->members) pair_ok = pair_ok && !eta_array(&c->d);
-  shapes.push_back({4, 4});
-  for (int k = 0; k < nshape - 1; ++k)
+  for (int k = 0; k < nshape; ++k)
     if (wave::stream_config_supported(kShapes[k][0], kShapes[k][1], !pair_ok))
       shapes.push_back({kShapes[k][0], kShapes[k][1]});
   if (pair_ok) {
     shapes.push_back({0, 16});
     shapes.push_back({0, 8});
   }
-  for (const auto& sh : shapes) {
-    int rc = wave_batch_set_kernel(b, sh[0], sh[1]);
+  shapes.push_back({4, 4});
+  // What a shape costs in a long run is what the later steps of a run add.  The first
+  // steps of a block group bring its state into the memory-side cache, which outweighs
+  // the rest of a short trial (12 bf16 shots of 150-220 cells, us: runs of 1, 3, 5, 9
+  // and 20 steps by size 396, 970, 1504, 2563, 5419, so 290 a step from the first two
+  // and 260 from the last two; in 128 x 8 tiles 284 and 288), and so does the GPU's
+  // clock in its first 10 ms.  So each shape takes one untimed step and is timed over
+  // two runs, whose difference counts per point update that the longer one has more:
+  // tiles over 1 and 1 + trial_steps steps, the layout by size over 4 and 12 or more,
+  // and last of all, after four untimed steps of it at the start.  No graphs
+  // meanwhile: their capture would be timed.
+  hipEvent_t e0 = nullptr, e1 = nullptr;
+  const int graph_steps = b->graph_steps;
+  auto leave = [&](int rc) {
+    b->graph_steps = graph_steps;
+    if (e0) (void)hipEventDestroy(e0);
+    if (e1) (void)hipEventDestroy(e1);
+    return rc;
+  };
+  hipError_t he = hipEventCreate(&e0);
+  if (he == hipSuccess) he = hipEventCreate(&e1);
+  if (he != hipSuccess) return leave(batch_fail(b, he, "hipEventCreate"));
+  b->graph_steps = 0;
+  auto timed = [&](int32_t n, double* ms, double* updates) -> int {
+    *updates = 0.0;
+    for (size_t i = 0; i < b->members.size(); ++i) {
+      const Layout& L = b->members[i]->L;
+      *updates += (double)L.nx * L.ny * L.nz * std::min(b->remaining[i], n);
+    }
+    hipError_t e = hipEventRecord(e0, b->user_stream);
+    if (e != hipSuccess) return batch_fail(b, e, "hipEventRecord");
+    const int rc = wave_batch_run(b, n);
     if (rc != WAVE_OK) return rc;
-    hipEvent_t e0, e1;
-    BCHK(b, hipEventCreate(&e0), "hipEventCreate");
-    BCHK(b, hipEventCreate(&e1), "hipEventCreate");
-    BCHK(b, hipEventRecord(e0, b->user_stream), "hipEventRecord");
-    std::vector<hipEvent_t> marks;
-    b->marks = &marks;
-    rc = wave_batch_run(b, trial_steps);
-    b->marks = nullptr;
-    auto drop_marks = [&]() {
-      for (hipEvent_t ev : marks) (void)hipEventDestroy(ev);
-      marks.clear();
-    };
-    if (rc != WAVE_OK) {
-      drop_marks();
-      (void)hipEventDestroy(e0);
-      (void)hipEventDestroy(e1);
-      return rc;
+    float t = 0.0f;
+    e = hipEventRecord(e1, b->user_stream);
+    if (e == hipSuccess) e = hipEventSynchronize(e1);
+    if (e == hipSuccess) e = hipEventElapsedTime(&t, e0, e1);
+    if (e != hipSuccess) return batch_fail(b, e, "tuning");
+    *ms = t;
+    return WAVE_OK;
+  };
+  std::array<int, 2> pick = {4, 4};
+  double best = 0.0;
+  int rc = wave_batch_set_kernel(b, 4, 4);
+  if (rc == WAVE_OK) rc = wave_batch_run(b, 4);
+  if (rc != WAVE_OK) return leave(rc);
+  for (const auto& sh : shapes) {
+    const bool by_size = sh[0] == 4;
+    const int32_t head = by_size ? 4 : 1, tail = by_size ? std::max(8, trial_steps) : trial_steps;
+    double t1 = 0.0, u1 = 0.0, t2 = 0.0, u2 = 0.0;
+    rc = wave_batch_set_kernel(b, sh[0], sh[1]);
+    if (rc == WAVE_OK) rc = wave_batch_run(b, 1);
+    if (rc == WAVE_OK) rc = timed(head, &t1, &u1);
+    if (rc == WAVE_OK) rc = timed(head + tail, &t2, &u2);
+    if (rc != WAVE_OK) return leave(rc);
+    // no steps left to compare on: by size
+    if (u2 <= u1) {
+      pick = {4, 4};
+      break;
     }
-    BCHK(b, hipEventRecord(e1, b->user_stream), "hipEventRecord");
-    BCHK(b, hipEventSynchronize(e1), "hipEventSynchronize");
-    float ms = 0.0f;
-    BCHK(b, hipEventElapsedTime(&ms, e0, e1), "hipEventElapsedTime");
-    // A block group's first step fills the memory-side cache for the others: it
-    // counts like one of them, as it does over the steps of a whole run (64 float32
-    // shots of 128-384 cells: two trial steps picked 64 x 8 tiles, 245 Gpoints/s,
-    // where the layout by size runs 285).
-    for (size_t i = 0; i + 2 < marks.size(); i += 3) {
-      float first = 0.0f, rest = 0.0f;
-      if (hipEventElapsedTime(&first, marks[i], marks[i + 1]) == hipSuccess &&
-          hipEventElapsedTime(&rest, marks[i + 1], marks[i + 2]) == hipSuccess)
-        ms -= std::max(0.0f, first - rest / (float)std::max(1, trial_steps - 1));
-    }
-    drop_marks();
-    (void)hipEventDestroy(e0);
-    (void)hipEventDestroy(e1);
-    if (best == 0.0f || ms < best * 0.985f) {   // as in wave_tune
-      best = ms;
-      pr = sh[0];
-      pn = sh[1];
+    const double per = t2 > t1 ? (t2 - t1) / (u2 - u1) : t2 / u2;
+    // as in wave_tune; a tile stays against the layout by size only where it is as
+    // much faster
+    if (best == 0.0 || (by_size ? per * 0.985 < best : per < best * 0.985)) {
+      best = per;
+      pick = sh;
     }
   }
-  const int rc = wave_batch_set_kernel(b, pr, pn);
-  if (rc != WAVE_OK) return rc;
-  if (chosen) {
-    chosen[0] = pr;
-    chosen[1] = pn;
+  rc = wave_batch_set_kernel(b, pick[0], pick[1]);
+  if (rc == WAVE_OK && chosen) {
+    chosen[0] = pick[0];
+    chosen[1] = pick[1];
   }
-  return WAVE_OK;
+  return leave(rc);
 }
 
 int wave_batch_free(wave_batch* b) {

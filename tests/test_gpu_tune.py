@@ -81,3 +81,49 @@ def test_tuning_fits_the_trace_buffer_it_fitted_before(W):
         rc, _ = W.wave_tune(sh.ctx, 2)
         assert (rc == W.WAVE_OK) == ok, (room, full)
         sh.close()
+
+
+def sizes(count, lo, hi, seed):
+    return [tuple(int(v) for v in r) for r in np.random.default_rng(seed).integers(lo, hi + 1, (count, 3))]
+
+
+def batch(W, members, steps, storage="f32", graph=0):
+    shots = [shot(W, nx, ny, nz, min(20, min(nx, ny, nz) // 4), max(8, steps), storage) for nx, ny, nz in members]
+    b = W.Batch(storage=storage, max_shots=len(shots))
+    b.set_graph(graph)
+    for sh in shots:
+        b.add(sh, steps)
+    return b, shots
+
+
+@pytest.mark.parametrize("storage", ["f32", "bf16", "f16"])
+def test_tuning_a_batch_keeps_its_speed(W, storage):
+    """Shots whose states together are several times the memory-side cache: the
+    first step of a run costs the layout by size more than its later ones."""
+    members = sizes(12, 150, 220, 5)
+    say(f"case tuned batch {storage}")
+    b, shots = batch(W, members, 2000, storage, graph=10)
+    cfgs = [tuple(b.tune(2)) for _ in range(3)]
+
+    def under(cfg):
+        def run(n):
+            b.set_kernel(*cfg)
+            b.run(n)
+        return run, b.stream
+    by_size, *tuned = least_us([under((4, 4))] + [under(c) for c in cfgs], 60, reps=3)
+    b.close()
+    for sh in shots:
+        sh.close()
+    say(f"by size {by_size:.1f}, tuned {cfgs} {[round(t, 1) for t in tuned]} us a step")
+    assert max(tuned) < 1.06 * by_size, (storage, cfgs, tuned, by_size)
+
+
+def test_members_without_steps_end_the_trials(W):
+    """A shape that no step is left for is not the fastest."""
+    say("case tuner without steps")
+    b, shots = batch(W, sizes(3, 30, 50, 2), 6)
+    assert tuple(b.tune(3)) == (4, 4)
+    assert all(b.remaining(sh) == 0 for sh in shots)
+    b.close()
+    for sh in shots:
+        sh.close()
