@@ -476,8 +476,9 @@ int wave_batch_remaining(const wave_batch *b, const wave_ctx *ctx, int32_t *rema
  * sources, run it here; the others 64 x 8 tiles, or 128 x 8 with two points per
  * lane (16-bit storage, no eta array, no stochastic rounding).  Block-kernel
  * members whose states together fit the memory-side cache take their steps of a
- * run together, one group of members after the other; their launches are never
- * captured, and need no second launch for sources and receivers. */
+ * run together, one group of members after the other (a run of one step takes as
+ * many as a launch holds); their launches are never captured, and need no second
+ * launch per step for sources and receivers. */
 int wave_batch_set_kernel(wave_batch *b, int32_t rows_per_wave, int32_t waves_per_group);
 int wave_batch_set_graph(wave_batch *b, int32_t steps_per_graph);
 

@@ -227,13 +227,14 @@ hipError_t launch_sweep_batch_pair(const BatchShot* shots, BatchState* state, in
 bool block_config_supported(int ty, int zc, const SweepArgs& a, int storage);
 // The same for several members of a batch, 4 x 4 blocks, or (duo) 8 x 4.  block_batch_grid sizes
 // a member's share of a launch (workgroups; a multiple of 8).  All members of a
-// launch share lm: 0 damping off, 1 eta array, 2 tables.  launch_record_members
-// samples the receivers of the members' u^n.
+// launch share lm: 0 damping off, 1 eta array, 2 tables.  launch_record_last samples
+// the receivers of the last step of the first n members of the tables, which must
+// hold their states at the start of the run.
 int block_batch_grid(const SweepArgs& a, bool duo, int nrec, BlockGrid* g);
 hipError_t launch_sweep_block_batch(const BatchShot* shots, const BlockBatch& bb, int storage,
                                     int lm, bool duo, hipStream_t s);
-hipError_t launch_record_members(const BatchShot* shots, const BlockBatch& bb, int storage,
-                                 hipStream_t s);
+hipError_t launch_record_last(const BatchShot* shots, const BatchState* state, int n, int storage,
+                              hipStream_t s);
 // Bytes of the state a sweep touches.
 int64_t sweep_footprint(int nx, int ny, int nz, int w, bool damping, bool eta_array, int es);
 // The block a grid's default launch uses; 0, 0 where the streaming kernels

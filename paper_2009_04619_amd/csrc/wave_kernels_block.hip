@@ -721,13 +721,18 @@ __global__ __launch_bounds__(256, 4) void k_sweep_block_batch(const BatchShot* _
     block_sweep<S, 64, 4, 4, LM, false>(a, e.io, sm.wide, e.g, local & 7, local >> 3);
 }
 
+// Receivers of the last step of a run, one workgroup per member; the members'
+// states in the table are those at its start.
 template <class S>
-__global__ __launch_bounds__(256) void k_record_members(const BatchShot* __restrict__ shots,
-                                                        BlockBatch bb) {
-  const BlockBatch::Member& e = bb.m[blockIdx.y];
-  SweepArgs a = shots[blockIdx.y].sa;
-  a.cur = shots[blockIdx.y].u[e.cur];
-  record_row<S>(a, e.io, blockIdx.x * 256 + threadIdx.x);
+__global__ __launch_bounds__(256) void k_record_last(const BatchShot* __restrict__ shots,
+                                                     const BatchState* __restrict__ state) {
+  using T = typename S::T;
+  const BatchShot& b = shots[blockIdx.x];
+  const BatchState& st = state[blockIdx.x];
+  if (b.target < 1) return;
+  const T* u = static_cast<const T*>(b.u[st.cur ^ (b.target & 1)]);
+  double* row = b.inj.traces + (int64_t)(st.trace_row + b.target - 1) * b.inj.nrec;
+  for (int r = threadIdx.x; r < b.inj.nrec; r += blockDim.x) row[r] = (double)S::ld(u, b.inj.rec_off[r]);
 }
 
 // 4 x 4 blocks are 64 points wide, or 32 x 8 where that saves a sixth of the lanes
@@ -897,17 +902,14 @@ hipError_t launch_sweep_block_batch(const BatchShot* shots, const BlockBatch& bb
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_record_members(const BatchShot* shots, const BlockBatch& bb, int storage,
-                                 hipStream_t s) {
-  int most = 0;
-  for (int i = 0; i < bb.n; ++i) most = std::max(most, bb.m[i].io.nrec);
-  if (most == 0) return hipSuccess;
-  const dim3 grid((unsigned)cdiv(most, 256), (unsigned)bb.n);
+hipError_t launch_record_last(const BatchShot* shots, const BatchState* state, int n, int storage,
+                              hipStream_t s) {
+  const dim3 grid((unsigned)n);
   switch (storage) {
-    case 0: hipLaunchKernelGGL(k_record_members<StF32>, grid, dim3(256), 0, s, shots, bb); break;
+    case 0: hipLaunchKernelGGL(k_record_last<StF32>, grid, dim3(256), 0, s, shots, state); break;
     case 1:
-    case 3: hipLaunchKernelGGL(k_record_members<StBF16>, grid, dim3(256), 0, s, shots, bb); break;
-    case 2: hipLaunchKernelGGL(k_record_members<StF16>, grid, dim3(256), 0, s, shots, bb); break;
+    case 3: hipLaunchKernelGGL(k_record_last<StBF16>, grid, dim3(256), 0, s, shots, state); break;
+    case 2: hipLaunchKernelGGL(k_record_last<StF16>, grid, dim3(256), 0, s, shots, state); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

@@ -524,13 +524,17 @@ wave::InjectArgs inject_args(const wave_ctx* c) {
 // Sources and receivers that a sweep launch takes along: the sources' places
 // (at most kStepSrc; unused entries match no point), their samples of step n,
 // and the receivers of u^n, trace row `row`, if there is one to sample.
-wave::StepIO step_sources(const wave_ctx* c) {
+wave::StepIO no_sources() {
   wave::StepIO io;
   memset(&io, 0, sizeof(io));
+  for (int32_t& z : io.sz) z = -1;
+  return io;
+}
+
+wave::StepIO step_sources(const wave_ctx* c) {
+  wave::StepIO io = no_sources();
   io.nsrc = c->nsrc;
-  for (int s = 0; s < wave::kStepSrc; ++s) {
-    io.sz[s] = -1;
-    if (s >= c->nsrc) continue;
+  for (int s = 0; s < c->nsrc; ++s) {
     io.sx[s] = c->src_host[3 * s];
     io.sy[s] = c->src_host[3 * s + 1];
     io.sz[s] = c->src_host[3 * s + 2];
@@ -582,6 +586,9 @@ struct wave_batch {
   bool by_size;               // no tile set: each member's sweep is chosen by its size
   struct Group;
   std::vector<Group> groups;  // the members in launch order (batch_layout)
+  std::vector<wave::BlockGrid> grid;  // block-kernel members: their blocks
+  std::vector<int32_t> nwg;           // and workgroups (0: a streaming member)
+  bool tuning;                // one-step runs keep to the groups (wave_batch_run)
   bool layout_dirty;          // membership or tile shape changed
   int graph_steps;            // steps per captured graph (0 = plain launches)
   // captured step blocks, one per group and number of its active members K
@@ -596,7 +603,7 @@ struct wave_batch {
 
 // Members first .. first + count - 1 of a batch take all their steps of a run
 // together, one launch (and one for sources and receivers, unless `block`) per
-// step, before the next group starts.
+// step, before the next group starts.  Block groups come first.
 struct wave_batch::Group {
   int first, count;
   bool block;                 // the block kernel (lm: 0 damping off, 1 eta array, 2 tables)
@@ -604,8 +611,7 @@ struct wave_batch::Group {
   bool duo;                   // two points per lane (8 x 4 blocks)
   int ry, nw;                 // otherwise the streaming tile (ry 0: two points per lane)
   bool eta_any;               // some member holds a per-point eta array
-  std::vector<int64_t> prefix;        // workgroups of the first k members
-  std::vector<wave::BlockGrid> grid;  // block: each member's blocks
+  std::vector<int64_t> prefix;        // streaming: workgroups of the first k members
 };
 
 namespace {
@@ -738,6 +744,8 @@ int batch_kind(const wave_ctx* c) {
 // cache and stay together (two bf16 shots of 352 cells 199 us, 215 one by one).
 void batch_layout(wave_batch* b) {
   b->h_shots.resize(b->members.size());
+  b->grid.resize(b->members.size());
+  b->nwg.assign(b->members.size(), 0);
   b->groups.clear();
   int64_t bytes = 0;
   for (size_t i = 0; i < b->members.size(); ++i) {
@@ -780,9 +788,7 @@ void batch_layout(wave_batch* b) {
     e.target = 0;
     e.inj = inject_args(c);
     if (g.block) {
-      wave::BlockGrid bg;
-      g.prefix.push_back(g.prefix.back() + wave::block_batch_grid(e.sa, g.duo, c->nrec, &bg));
-      g.grid.push_back(bg);
+      b->nwg[i] = wave::block_batch_grid(e.sa, g.duo, c->nrec, &b->grid[i]);
       continue;
     }
     // rows_per_wave 0: two points per lane, 128 x nw tiles
@@ -859,49 +865,77 @@ hipError_t batch_run_stream(wave_batch* b, int group) {
   return hipSuccess;
 }
 
-// All steps of a block group, one launch each (what changes from step to step
-// travels in the launch's arguments, so these are never captured), and one for
-// the receivers of every member's last step.
-hipError_t batch_run_block(wave_batch* b, const wave_batch::Group& g) {
-  const wave::BatchShot* h = b->h_shots.data() + g.first;
+// All steps of block members first .. first + count - 1 (of one kind), one launch
+// each: what changes from step to step travels in the launch's arguments, so these
+// are never captured.  The sources of a step and the receivers of the step before
+// go with it, unless the caller sees to them (`alone`, one step).
+hipError_t batch_run_block(wave_batch* b, int first, int count, int lm, bool duo, bool alone) {
+  const wave::BatchShot* h = b->h_shots.data() + first;
   wave::BlockBatch bb;
   memset(&bb, 0, sizeof(bb));
-  for (int i = 0; i < g.count; ++i) {
-    const wave_ctx* c = b->members[g.first + i];
-    bb.m[i].g = g.grid[i];
-    bb.m[i].io = step_sources(c);
-    bb.begin[i] = (int32_t)g.prefix[i];
+  for (int i = 0; i < count; ++i) {
+    bb.m[i].g = b->grid[first + i];
+    bb.m[i].io = alone ? no_sources() : step_sources(b->members[first + i]);
+    bb.begin[i + 1] = bb.begin[i] + b->nwg[first + i];
   }
-  auto at_step = [&](int i, int32_t t) {   // member i before its step t of this run
-    const wave_ctx* c = b->members[g.first + i];
-    wave::BlockBatch::Member& m = bb.m[i];
-    m.cur = (c->icur < c->iprev ? 0 : 1) ^ (t & 1);
-    m.step = (int32_t)c->step + t;
-    step_samples(c, c->step + t, &m.io);
-    step_receivers(c, t > 0, c->trace_count + t - 1, &m.io);
-  };
-  int k = g.count;
+  int k = count;
   for (int32_t t = 0; t < h[0].target; ++t) {
     while (h[k - 1].target <= t) --k;
-    for (int i = 0; i < k; ++i) at_step(i, t);
+    for (int i = 0; i < k; ++i) {
+      const wave_ctx* c = b->members[first + i];
+      wave::BlockBatch::Member& m = bb.m[i];
+      m.cur = (c->icur < c->iprev ? 0 : 1) ^ (t & 1);
+      m.step = (int32_t)c->step + t;
+      step_samples(c, c->step + t, &m.io);
+      step_receivers(c, t > 0, c->trace_count + t - 1, &m.io);
+    }
     bb.n = k;
     bb.back = t & 1;
-    bb.begin[k] = (int32_t)g.prefix[k];
     hipError_t e;
     if (k == 1) {   // as on its own: no table to look up (2.5 us less)
       wave::SweepArgs a = h[0].sa;
       a.cur = h[0].u[bb.m[0].cur];
       a.nxt = h[0].u[bb.m[0].cur ^ 1];
       a.step = bb.m[0].step;
-      e = wave::launch_sweep_block(a, bb.m[0].io, b->kstore, g.duo ? 8 : 4, 4, b->stream);
+      e = wave::launch_sweep_block(a, bb.m[0].io, b->kstore, duo ? 8 : 4, 4, b->stream);
     } else {
-      e = wave::launch_sweep_block_batch(b->d_shots + g.first, bb, b->kstore, g.lm, g.duo, b->stream);
+      e = wave::launch_sweep_block_batch(b->d_shots + first, bb, b->kstore, lm, duo, b->stream);
     }
     if (e != hipSuccess) return e;
   }
-  for (int i = 0; i < g.count; ++i) at_step(i, h[i].target);
-  bb.n = g.count;
-  return wave::launch_record_members(b->d_shots + g.first, bb, b->kstore, b->stream);
+  return hipSuccess;
+}
+
+// All steps of the block groups, and the receivers of every member's last step.
+hipError_t batch_run_blocks(wave_batch* b, int32_t steps) {
+  size_t ng = 0;
+  int n = 0;   // members in block groups
+  for (; ng < b->groups.size() && b->groups[ng].block; ++ng) n += b->groups[ng].count;
+  if (n == 0) return hipSuccess;
+  if (steps > 1 || ng == 1 || b->tuning) {
+    for (size_t i = 0; i < ng; ++i) {
+      const wave_batch::Group& g = b->groups[i];
+      const hipError_t e = batch_run_block(b, g.first, g.count, g.lm, g.duo, false);
+      if (e != hipSuccess) return e;
+    }
+    return wave::launch_record_last(b->d_shots, b->d_state, n, b->kstore, b->stream);
+  }
+  // a run of one step comes back to no member's state: as many members to a launch
+  // as it takes, and one launch for all sources and receivers (24 float32 shots of
+  // 128-256 cells, us for such a run: group by group 1001, so 896, in 64 x 16 tiles
+  // together 902; 128 shots of 24-40 cells 150, 132, 143)
+  for (size_t i = 0; i < ng;) {
+    size_t j = i + 1;
+    while (j < ng && b->groups[j].lm == b->groups[i].lm && b->groups[j].duo == b->groups[i].duo) ++j;
+    const int end = b->groups[j - 1].first + b->groups[j - 1].count;
+    for (int m = b->groups[i].first; m < end; m += wave::kBlockMembers) {
+      const hipError_t e = batch_run_block(b, m, std::min(wave::kBlockMembers, end - m),
+                                           b->groups[i].lm, b->groups[i].duo, true);
+      if (e != hipSuccess) return e;
+    }
+    i = j;
+  }
+  return wave::launch_inject_batch(b->d_shots, b->d_state, n, b->kstore, b->stream);
 }
 
 }  // namespace
@@ -1309,13 +1343,7 @@ int wave_step(wave_ctx* c, int32_t n) {
   // the block kernel adds up to kStepSrc sources and samples the receivers of
   // the step before in its own launch; the last step's receivers follow it
   const bool fused = c->variant == WAVE_KERNEL_BLOCK && c->nsrc <= wave::kStepSrc;
-  wave::StepIO io;
-  if (fused) {
-    io = step_sources(c);
-  } else {
-    memset(&io, 0, sizeof(io));
-    for (int& z : io.sz) z = -1;
-  }
+  wave::StepIO io = fused ? step_sources(c) : no_sources();
   auto launch_one = [&](const wave::SweepArgs& s) -> hipError_t {
     if (c->variant == WAVE_KERNEL_BLOCK)
       return wave::launch_sweep_block(s, io, kernel_storage(&c->d), c->shp[1], c->shp[2], c->stream);
@@ -1898,6 +1926,7 @@ int wave_batch_create(int32_t storage, int32_t max_shots, void* dev_arena, size_
   b->ry = 1;
   b->nw = 16;
   b->by_size = true;
+  b->tuning = false;
   b->layout_dirty = true;
   b->graph_steps = 0;
   b->broken = false;
@@ -2085,10 +2114,10 @@ int wave_batch_run(wave_batch* b, int32_t n) {
     BCHK(b, hipEventRecord(b->ev_copy[k], b->stream), "hipEventRecord");
     b->runs += 1;
   }
-  for (size_t gi = 0; gi < b->groups.size(); ++gi) {
-    const hipError_t e = b->groups[gi].block ? batch_run_block(b, b->groups[gi]) : batch_run_stream(b, (int)gi);
-    if (e != hipSuccess) return batch_fail(b, e, "batch launch");
-  }
+  hipError_t e = batch_run_blocks(b, steps);
+  for (size_t gi = 0; gi < b->groups.size() && e == hipSuccess; ++gi)
+    if (!b->groups[gi].block) e = batch_run_stream(b, (int)gi);
+  if (e != hipSuccess) return batch_fail(b, e, "batch launch");
   BCHK(b, hipEventRecord(b->ev_out, b->stream), "hipEventRecord");
   BCHK(b, hipStreamWaitEvent(b->user_stream, b->ev_out, 0), "hipStreamWaitEvent");
   // host mirrors of each member's state after its `target` steps
@@ -2134,6 +2163,7 @@ int wave_batch_tune(wave_batch* b, int32_t trial_steps, int32_t chosen[2]) {
   const int graph_steps = b->graph_steps;
   auto leave = [&](int rc) {
     b->graph_steps = graph_steps;
+    b->tuning = false;
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
     return rc;
@@ -2142,6 +2172,7 @@ int wave_batch_tune(wave_batch* b, int32_t trial_steps, int32_t chosen[2]) {
   if (he == hipSuccess) he = hipEventCreate(&e1);
   if (he != hipSuccess) return leave(batch_fail(b, he, "hipEventCreate"));
   b->graph_steps = 0;
+  b->tuning = true;
   auto timed = [&](int32_t n, double* ms, double* updates) -> int {
     *updates = 0.0;
     for (size_t i = 0; i < b->members.size(); ++i) {

@@ -205,3 +205,24 @@ def test_block_tile_widths(W, nx, storage):
     got = run(W, shot, (2, 3), (10, 1, 4, 4), storage.replace("sr", ""), sr=storage == "bf16sr")
     for key in ("u", "u_prev", "phi", "traces"):
         assert np.array_equal(got[key], expect[key]), (nx, storage, key)
+
+
+@pytest.mark.parametrize("members", [MIXED, MANY, LARGE, HALF], ids=["mixed", "many", "large", "half"])
+def test_batch_runs_of_one_step(W, members):
+    """Runs of one step, which launch more members together than longer ones and add
+    sources and sample receivers apart, between longer ones; members that have ended
+    lie between those that have not."""
+    say(f"case batch one step a run, {len(members)} members")
+    n = [3 + (5 * i) % 7 for i in range(len(members))]
+    b = W.Batch(storage=members[0][7] if len(members[0]) > 7 else "f32", max_shots=len(members))
+    shots = [_shot(W, *m) for m in members]
+    for sh, k in zip(shots, n):
+        b.add(sh, k)
+    for k in (1, 1, 2, 1, 3, 1, 1, 1):
+        b.run(k)
+    for sh in shots:
+        assert b.remaining(sh) == 0
+    b.close()
+    for i, sh in enumerate(shots):
+        for x, y in zip(_state(W, sh), _solo(W, members[i], n[i])):
+            assert x.shape == y.shape and np.array_equal(x, y), (i, members[i])

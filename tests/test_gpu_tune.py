@@ -127,3 +127,24 @@ def test_members_without_steps_end_the_trials(W):
     b.close()
     for sh in shots:
         sh.close()
+
+
+def test_runs_of_one_step_by_size(W):
+    """A run of one step finds no member's state in the memory-side cache: without a
+    set tile it costs no more than the 64 x 16 tiles, which take every member in one
+    launch.  Five groups of members or more."""
+    say("case batch, one step a run")
+    b, shots = batch(W, sizes(20, 128, 256, 11), 2000)
+
+    def under(cfg):
+        def run(n):
+            b.set_kernel(*cfg)
+            for _ in range(n):
+                b.run(1)
+        return run, b.stream
+    by_size, tile = least_us([under((4, 4)), under((1, 16))], 30, reps=3)
+    b.close()
+    for sh in shots:
+        sh.close()
+    say(f"by size {by_size:.1f}, 64 x 16 tiles {tile:.1f} us a step")
+    assert by_size < 1.04 * tile
