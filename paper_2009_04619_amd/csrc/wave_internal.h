@@ -136,10 +136,12 @@ struct BatchState {
 // mulhi divides (exact for dividend * divisor < 2^32, checked by the launcher).
 struct BlockGrid {
   int32_t tiles_x, tiles_y;
-  int32_t slab;      // most tile rows of an XCD in a layer of blocks
+  int32_t run;       // 0: slabs; else rows of blocks in an XCD's run (block_at)
+  int32_t layers;    // layers of blocks
+  int32_t slab;      // most tile rows of an XCD in a layer of blocks; runs: tile rows
   int32_t half;      // first layer of the upper half
-  int32_t per_xcd;   // blocks per XCD, slab padding included
-  uint32_t mx, mslab;
+  int32_t per_xcd;   // blocks per XCD, padding included
+  uint32_t mx, mrow; // of tiles_x and slab
   int narrow;        // 32 x 8 x 4 points per block, else 64 wide
 };
 

@@ -563,19 +563,23 @@ __device__ __forceinline__ int div_by(int n, int d, uint32_t m) {
   return d == 1 ? n : (int)__umulhi((uint32_t)n, m);
 }
 
-// Tile and layer of block `at` of XCD xcd; false: slab padding.  An XCD takes one
+// Tile and layer of block `at` of XCD xcd; false: padding.  An XCD takes one
 // slab of tile rows through the layers of blocks, so neighbouring blocks read
 // their halos from one L2 (8 % faster at 256^3 than a contiguous run of layers
 // per XCD).  Where the tile rows do not divide by 8 the slabs differ by a row;
 // in the upper half of the layers every XCD takes the next one's, which evens
-// them out.
+// them out.  Few tile rows do not make 8 slabs of about one size, and leave XCDs
+// idle: there each takes a run of consecutive rows of blocks (block_grid).
 __device__ __forceinline__ bool block_at(const BlockGrid& g, int xcd, int at, int* tx, int* ty,
                                          int* zl) {
   const int t2 = div_by(at, g.tiles_x, g.mx);
   *tx = at - t2 * g.tiles_x;
-  *zl = div_by(t2, g.slab, g.mslab);
+  const int r = t2 + xcd * g.run;
+  *zl = div_by(r, g.slab, g.mrow);
+  *ty = r - *zl * g.slab;
+  if (g.run) return *zl < g.layers;
   const int k = (xcd + (*zl >= g.half ? 1 : 0)) & 7;
-  *ty = (k * g.tiles_y >> 3) + t2 - *zl * g.slab;
+  *ty += k * g.tiles_y >> 3;
   return *ty < ((k + 1) * g.tiles_y >> 3);
 }
 
@@ -754,14 +758,35 @@ bool block_grid(const SweepArgs& a, int tw, int ty, int zc, BlockGrid* g) {
   g->slab = cdiv(g->tiles_y, 8);
   const int layers = chunk_count(a.nz, a.w, zc, a.damping != 0);
   g->half = cdiv(layers, 2);
-  const int64_t n = (int64_t)g->tiles_x * g->slab * layers;
+  // Runs where slabs load the busiest XCD by more than 8 % more; us per step, slabs ->
+  // runs, with the loads' ratio: 8 x 4 bf16 2939 x 5 x 2041 398 -> 123 (4.0), 774 x 72 x
+  // 537 109 -> 83 (1.33); 4 x 4 float32 1039 x 20 x 721 80 -> 49 (1.6), 70x45x37 4.3 ->
+  // 4.0 (1.22); 8 x 8 without a layer 500 x 200 x 500 146 -> 146, bf16 112 -> 99 (1.12).
+  // Also where slabs of a few rows share little: blocks of 4 rows up to 160 rows of
+  // points (580 x 64 x 403 58 -> 48, 96^3 5.9 -> 5.4, 300 x 160 x 200 35.7 -> 34.9; 376 x
+  // 152 x 261 47.8 -> 48.1), of 8 x 4 up to 112 (670 x 96 x 465 84 -> 79, 621 x 112 x 431
+  // 81 -> 77; 600 x 120 x 416 79.5 -> 80).  Elsewhere slabs: 8 x 8 948 x 64 x 658 110.1 ->
+  // 110.8 and 512^3 358 -> 401, 4 x 4 192^3 with an eta array 28.7 -> 29.1 and 256^3 54.4
+  // -> 63.8, 8 x 4 256^3 42.4 -> 43.4.
+  const int64_t rows = (int64_t)g->tiles_y * layers;
+  auto slab_rows = [&](int k) { return ((k + 1) * g->tiles_y >> 3) - (k * g->tiles_y >> 3); };
+  int64_t most = 0;
+  for (int k = 0; k < 8; ++k)
+    most = std::max(most, (int64_t)g->half * slab_rows(k) + (int64_t)(layers - g->half) * slab_rows((k + 1) & 7));
+  const int64_t run = (rows + 7) / 8;
+  const bool runs = 25 * most > 27 * run || (zc == 4 && a.ny <= (tw == kTX && ty == kDY ? 112 : 160));
+  const int64_t n = g->tiles_x * (runs ? run : (int64_t)g->slab * layers);
   if ((int64_t)(zc + 2 * kR) * a.plane * 4 > kWindowMax ||
-      n * std::max(g->tiles_x, g->slab) >= (int64_t(1) << 32) || n > 0x07ffffff)
+      n * std::max(g->tiles_x, g->slab) >= (int64_t(1) << 32) || n > 0x07ffffff ||
+      (runs && 8 * run * g->tiles_y >= (int64_t(1) << 32)))  // rows of blocks by layers
     return false;
+  g->run = runs ? (int32_t)run : 0;
+  g->layers = layers;
+  if (runs) g->slab = g->tiles_y;
   g->per_xcd = (int)n;
   auto magic = [](int d) { return (uint32_t)(0xffffffffu / (uint32_t)d + 1u); };
   g->mx = magic(g->tiles_x);
-  g->mslab = magic(g->slab);
+  g->mrow = magic(g->slab);
   g->narrow = tw == 32;
   return true;
 }

@@ -226,3 +226,45 @@ def test_batch_runs_of_one_step(W, members):
     for i, sh in enumerate(shots):
         for x, y in zip(_state(W, sh), _solo(W, members[i], n[i])):
             assert x.shape == y.shape and np.array_equal(x, y), (i, members[i])
+
+
+# few rows of blocks, which XCDs take in runs: 1 to 7, 9 and 10 tile rows of 4 and of 8,
+# with the last run ending in, at and past the last row
+THIN = [(70, 3, 40, 1, "f32", True), (66, 5, 21, 2, "f32", True), (130, 9, 33, 3, "bf16", True),
+        (65, 17, 26, 5, "f16", True), (200, 20, 18, 4, "f32", True), (90, 33, 25, 8, "bf16sr", True),
+        (64, 36, 30, 3, "f32", True), (129, 40, 22, 6, "bf16", True), (64, 72, 19, 5, "f16", True),
+        (70, 5, 41, 0, "f32", False), (66, 9, 65, 0, "bf16", False), (40, 72, 9, 0, "f32", False),
+        (33, 1, 50, 0, "f16", False), (1, 2, 9, 0, "f32", False)]
+
+
+def _run_state(W, grid, kernel, steps, dt=2e-4, eta=False):
+    """Fields and traces after `steps` from a random state, under `kernel`."""
+    nx, ny, nz, w, storage, damping = grid
+    rng = np.random.default_rng(nx + 3 * ny + nz)
+    vel = rng.uniform(1500.0, 4000.0, (nz, ny, nx)).astype(np.float32)
+    e = rng.uniform(0.0, 0.3, (nz, ny, nx)).astype(np.float32) if eta else None
+    sh = W.Shot(nx, ny, nz, w, 10.0, 10.0, 10.0, dt, vel, eta=e, damping=damping, max_src=2, max_rec=90, max_steps=16,
+                storage=storage.replace("sr", ""), stochastic_round=storage.endswith("sr"))
+    for p in ((nx - 1, ny - 1, nz - 1), (nx // 2, ny // 2, nz // 2)):
+        sh.inject(*p, rng.standard_normal(16).astype(np.float32))
+    sh.record(np.stack([rng.integers(0, n, 90) for n in (nx, ny, nz)], axis=1))
+    for which in [W.WAVE_FIELD_U, W.WAVE_FIELD_UPREV] + ([W.WAVE_FIELD_PHI] if damping else []):
+        sh.write(which, rng.standard_normal((nz, ny, nx)).astype(np.float32))
+    if kernel:
+        sh.set_kernel(*kernel)
+    for n in steps:
+        sh.step(n)
+    return _state(W, sh)
+
+
+@pytest.mark.parametrize("grid", THIN, ids=lambda g: f"{g[0]}x{g[1]}x{g[2]}_w{g[3]}_{g[4]}")
+def test_thin_grids(W, grid):
+    storage, damping = grid[4:]
+    sr = storage == "bf16sr"
+    expect = _run_state(W, grid, (0, 1, 1, 0), (5,))
+    kernels = [(10, 1, 4, 4)] + ([] if damping or sr else [(10, 1, 8, 8)]) + \
+        ([(10, 1, 8, 4)] if storage in ("bf16", "f16") else [])
+    for k in kernels:
+        say(f"case block thin {k} grid {grid}")
+        for x, y in zip(_run_state(W, grid, k, (2, 3)), expect):
+            assert np.isfinite(y).all() and np.array_equal(x, y), (k, grid)
