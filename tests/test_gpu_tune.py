@@ -152,10 +152,12 @@ def test_runs_of_one_step_by_size(W):
 
 @pytest.mark.parametrize("nx,ny,nz,w,storage", [(1500, 5, 1000, 2, "bf16"), (1100, 9, 800, 3, "bf16"),
                                                 (1500, 5, 1000, 2, "f32"), (1030, 33, 730, 10, "bf16"),
-                                                (2500, 9, 1750, 0, "f32"), (1320, 33, 917, 0, "f32")])
+                                                (2500, 9, 1750, 0, "f32"), (1320, 33, 917, 0, "f32"),
+                                                (1900, 1320, 9, 0, "f32"), (1840, 1280, 17, 0, "f32"),
+                                                (3100, 2150, 9, 0, "bf16")])
 def test_default_launch_of_thin_grids(W, nx, ny, nz, w, storage):
-    """Few rows of tiles: the default launch keeps all XCDs busy, and is not behind
-    one workgroup per 64 x 8 streaming tile."""
+    """Few rows of tiles, and one plane past whole layers of blocks: the default launch
+    is not behind one workgroup per 64 x 8 streaming tile."""
     say(f"case thin {nx}x{ny}x{nz} {storage}")
     sh = shot(W, nx, ny, nz, w, 2000, storage, damping=w > 0)
     other = shot(W, nx, ny, nz, w, 2000, storage, damping=w > 0)
