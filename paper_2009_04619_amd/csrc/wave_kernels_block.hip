@@ -858,9 +858,11 @@ void block_default(const SweepArgs& a, int storage, int* ty, int* zc) {
   *ty = *zc = 0;
   // one plane past whole layers of 8 costs as much as 8 (us per step against the
   // streaming tiles: float32 2529 x 1756 x 9 181 / 170, 1840 x 1278 x 17 157 / 145, 1321
-  // x 917 x 33 132 / 128, 1185 x 823 x 41 127 / 128; bf16 3098 x 2151 x 9 206 / 193, 2254
-  // x 1565 x 17 166 / 169; four planes past, float32 2104 x 1461 x 13, 136 / 151)
-  const bool one_more = a.nz % 8 == 1 && a.nz < (es == 4 ? 40 : 16);
+  // x 917 x 33 132 / 128, 1185 x 823 x 41 127 / 128, and of less state 1380 x 958 x 17
+  // 84 / 81, 1138 x 790 x 25 77 / 80; bf16 3098 x 2151 x 9 206 / 193, 2254 x 1565 x 17
+  // 166 / 169; four planes past, float32 2104 x 1461 x 13, 136 / 151)
+  const bool one_more = a.nz % 8 == 1 && a.nz > 1 &&
+                        a.nz < (es == 2 ? 16 : bytes > 280 * 1000000LL ? 40 : 24);
   const bool duo = es == 2 && storage != 3 && !a.eta && bytes > 10 * 1000000LL &&
                    bytes <= (a.damping ? 360 : 280) * 1000000LL;
   if (duo) {
