@@ -335,7 +335,7 @@ int wave_energy_noalloc(wave_ctx *ctx, double *dev_out);
                                 receivers in the same launch; rows_per_wave =
                                 1, (waves_per_group, zchunk) = (ty, zc): (4,4),
                                 run as 32 x 8 x 4 points where 64-wide blocks
-                                leave half a tile idle (3 or 5 tiles of 32);
+                                leave half a tile idle (1, 3 or 5 tiles of 32);
                                 (8,4), two points per lane, with 16-bit storage,
                                 no eta array and no stochastic rounding; (8,8)
                                 with damping off and no stochastic rounding;

@@ -740,15 +740,18 @@ __global__ __launch_bounds__(256) void k_record_last(const BatchShot* __restrict
 }
 
 // 4 x 4 blocks are 64 points wide, or 32 x 8 where that saves a sixth of the lanes
-// or more: with 3 or 5 tiles of 32 columns (65..96 and 129..160 points in x) 64-wide
-// tiles leave a half tile idle.  us per step, 64 -> 32 wide: 70x45x37 5.05 -> 4.85,
+// or more: with 1, 3 or 5 tiles of 32 columns (1..32, 65..96 and 129..160 points in x)
+// 64-wide tiles leave a half tile idle.  us per step, 64 -> 32 wide: 70x45x37 5.05 -> 4.85,
 // 96^3 7.05 -> 6.6 (no layer 5.9 -> 5.3), 160^3 16.8 -> 15.6 (no layer 12.8 -> 11.3),
 // 160^3 in f16 16.7 -> 14.3 and stochastic bf16 18.0 -> 16.4.  With 7 tiles the
 // saving no longer decides (224^3 37.4..39.9 -> 38.3..39.4), and where it saves none,
-// 32-wide tiles read more x halo (176x144x160 16.6 -> 17.5, 256^3 55 -> 56.4).
+// 32-wide tiles read more x halo (176x144x160 16.6 -> 17.5, 256^3 55 -> 56.4).  Up to
+// 32 points half of every wavefront was idle: 9 x 1420 x 1173 316 -> 224 (64 x 8
+// streaming tiles 288), 32 x 753 x 622 84 -> 59, 30 x 100 x 100 5.1 -> 4.4 and bf16 5.1
+// -> 4.6; below 64^2 rows a launch is too short to gain (bf16 32^3 3.9 -> 4.3).
 bool narrow_blocks(const SweepArgs& a) {
   const int tiles = cdiv(a.nx, 32);
-  return tiles == 3 || tiles == 5;
+  return tiles == 3 || tiles == 5 || (tiles == 1 && (int64_t)a.ny * a.nz >= 4096);
 }
 
 // false: the grid does not fit the index arithmetic.

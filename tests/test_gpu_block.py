@@ -268,3 +268,20 @@ def test_thin_grids(W, grid):
         say(f"case block thin {k} grid {grid}")
         for x, y in zip(_run_state(W, grid, k, (2, 3)), expect):
             assert np.isfinite(y).all() and np.array_equal(x, y), (k, grid)
+
+
+@pytest.mark.parametrize("nx", [1, 9, 31, 32, 33])
+@pytest.mark.parametrize("storage", ["f32", "bf16", "f16", "bf16sr"])
+def test_narrow_grids(W, nx, storage):
+    """Grids one block of 32 columns wide, either side of the count of rows from which
+    blocks take them, with a layer, without, and with an eta array."""
+    w = min(4, nx // 2)
+    for ny, nz in ((64, 64), (63, 65), (37, 150)):
+        for damping, eta in ((True, False), (False, False), (True, True)):
+            if w == 0 and damping:
+                continue
+            say(f"case narrow {nx}x{ny}x{nz} {storage} damping {damping} eta {eta}")
+            grid = (nx, ny, nz, w if damping else 0, storage, damping)
+            got, expect = (_run_state(W, grid, k, (2, 1), eta=eta) for k in ((10, 1, 4, 4), (0, 1, 1, 0)))
+            for x, y in zip(got, expect):
+                assert np.isfinite(y).all() and np.array_equal(x, y), grid

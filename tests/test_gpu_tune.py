@@ -154,10 +154,11 @@ def test_runs_of_one_step_by_size(W):
                                                 (1500, 5, 1000, 2, "f32"), (1030, 33, 730, 10, "bf16"),
                                                 (2500, 9, 1750, 0, "f32"), (1320, 33, 917, 0, "f32"),
                                                 (1900, 1320, 9, 0, "f32"), (1840, 1280, 17, 0, "f32"),
-                                                (3100, 2150, 9, 0, "bf16")])
+                                                (3100, 2150, 9, 0, "bf16"),
+                                                (9, 1420, 1170, 4, "f32"), (16, 1060, 880, 8, "f32")])
 def test_default_launch_of_thin_grids(W, nx, ny, nz, w, storage):
-    """Few rows of tiles, and one plane past whole layers of blocks: the default launch
-    is not behind one workgroup per 64 x 8 streaming tile."""
+    """Few rows of tiles, one plane past whole layers of blocks, few columns: the
+    default launch is not behind one workgroup per 64 x 8 streaming tile."""
     say(f"case thin {nx}x{ny}x{nz} {storage}")
     sh = shot(W, nx, ny, nz, w, 2000, storage, damping=w > 0)
     other = shot(W, nx, ny, nz, w, 2000, storage, damping=w > 0)
