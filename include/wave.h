@@ -351,7 +351,8 @@ int wave_energy_noalloc(wave_ctx *ctx, double *dev_out);
  * points per lane), and with damping off and no stochastic rounding on larger
  * grids too; else, with 16-bit
  * storage and no eta array, WAVE_KERNEL_PAIR with 8 rows (with stochastic
- * rounding 16 rows, and only on the large grids of the next clause); else
+ * rounding 16 rows, and only on the large grids of the next clause; up to 64 and
+ * from 129 to 192 columns WAVE_KERNEL_STREAM with (1,8) tiles instead); else
  * WAVE_KERNEL_PERSIST with (1,16) tiles and its automatic chunk (half the
  * streaming kernel's) on grids large enough for 64-plane chunks of 64 x 16 tiles
  * with about 2048 workgroups (512^3 and up for cubes), else WAVE_KERNEL_STREAM
@@ -474,7 +475,8 @@ int wave_batch_remaining(const wave_batch *b, const wave_ctx *ctx, int32_t *rema
  * a set tile, and (4, 4) returns to that: each member's sweep is then chosen by
  * its size.  Members that run WAVE_KERNEL_BLOCK by default, with at most 4
  * sources, run it here; the others 64 x 8 tiles, or 128 x 8 with two points per
- * lane (16-bit storage, no eta array, no stochastic rounding).  Block-kernel
+ * lane (16-bit storage, no eta array, no stochastic rounding, neither up to 64 nor
+ * from 129 to 192 columns).  Block-kernel
  * members whose states together fit the memory-side cache take their steps of a
  * run together, one group of members after the other (a run of one step takes as
  * many as a launch holds); their launches are never captured, and need no second

@@ -698,6 +698,18 @@ int pair_zchunk(const wave_ctx* c, int ty, int zchunk, int semi_nw = 0) {
   return std::min(zc, lim);
 }
 
+// Whether 128-wide tiles leave so many lanes idle that 64 x 8 tiles of one point per
+// lane are the faster ones for 16-bit storage: with one tile of 64 columns or three
+// (bf16, us per step, 128 x 8 / 64 x 8: 64 x 945 x 826 204 / 177, 48 x 1092 x 953 261 /
+// 240, 129 x 1074 x 938 592 / 535, 160 x 598 x 522 173 / 156, 192 x 880 x 769 352 / 343,
+// stochastic 129 x 1074 x 938 692 in 128 x 16 / 572; against that 56 x 1630 x 1423 629 /
+// 649 and 176 x 919 x 803 407 / 414).  With five the two are even (257 to 320 columns
+// 0.94 to 1.03), with two or four every width measured gains.
+bool pair_idle(const wave_ctx* c) {
+  const int tiles = (c->L.nx + wave::kTX - 1) / wave::kTX;
+  return tiles == 1 || tiles == 3;
+}
+
 // State of a member that its sweep touches, and what a group of several members
 // may hold to stay in the 256 MB memory-side cache between steps (8 float32
 // shots of 128-256 cells, 46-145 MB each, us per step at 100, 150, 200, 240,
@@ -726,12 +738,15 @@ bool batch_block_member(const wave_ctx* c, bool* duo) {
 }
 
 // Launch order of a member in a batch without a set tile: members of one kind
-// can share a launch.
+// can share a launch.  Streaming kinds: two points per lane, one, one with an eta
+// array.
 constexpr int kStreamKind = 6;
 int batch_kind(const wave_ctx* c) {
   const int lm = !c->damp ? 0 : eta_array(&c->d) ? 1 : 2;
   bool duo = false;
-  return batch_block_member(c, &duo) ? lm + (duo ? 3 : 0) : kStreamKind + (lm == 1 ? 1 : 0);
+  if (batch_block_member(c, &duo)) return lm + (duo ? 3 : 0);
+  if (lm == 1) return kStreamKind + 2;
+  return kStreamKind + (c->es == 2 && kernel_storage(&c->d) != 3 && !pair_idle(c) ? 0 : 1);
 }
 
 // Rebuild the member tables (static part) and the groups; targets are filled
@@ -767,7 +782,7 @@ void batch_layout(wave_batch* b) {
       g.ry = b->ry;
       g.nw = b->nw;
       if (b->by_size) {
-        g.ry = c->es == 2 && b->kstore != 3 && pair_zchunk(c, 8, 0) >= 1 ? 0 : 1;
+        g.ry = kind == kStreamKind ? 0 : 1;
         g.nw = 8;
       }
       g.eta_any = false;
@@ -1096,12 +1111,16 @@ int wave_alloc(const wave_desc* d, const float* vel, const float* eta, void* dev
     // 128 x 16 tiles, which win on large grids (512^3 327 / 354; 448^3 255 / 236)
     const bool sr = kernel_storage(d) == 3;
     const int pty = sr ? 16 : 8;
+    const bool pair = c->es == 2 && (large || !sr) && pair_zchunk(c, pty, 0) >= 1;
     if (bty) {
       c->variant = WAVE_KERNEL_BLOCK;
       c->shp[0] = 1;
       c->shp[1] = bty;
       c->shp[2] = bzc;
-    } else if (c->es == 2 && (large || !sr) && pair_zchunk(c, pty, 0) >= 1) {
+    } else if (pair && pair_idle(c)) {
+      c->variant = WAVE_KERNEL_STREAM;
+      c->nw = 8;
+    } else if (pair) {
       c->variant = WAVE_KERNEL_PAIR;
       c->shp[0] = 1;
       c->shp[1] = pty;

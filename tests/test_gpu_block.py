@@ -207,6 +207,52 @@ def test_block_tile_widths(W, nx, storage):
         assert np.array_equal(got[key], expect[key]), (nx, storage, key)
 
 
+# 16-bit members that stream: two points per lane, one where 128-wide tiles leave half of
+# them idle, and one with an eta array; among them members of the block kernel
+STREAM16 = [(100, 40, 30, 4, 6, False, True, "bf16"), (60, 40, 30, 4, 6, False, True, "bf16"),
+            (131, 30, 26, 4, 5, False, True, "bf16"), (64, 33, 20, 0, 7, False, False, "bf16"),
+            (70, 30, 30, 4, 5, True, True, "bf16"), (200, 24, 22, 4, 5, False, True, "bf16"),
+            (50, 30, 30, 4, 2, False, True, "bf16")]
+
+
+def _member(W, nx, ny, nz, w, nsrc, eta, damping, storage):
+    """A member from a random state, `storage` "bf16sr" for stochastic rounding."""
+    rng = np.random.default_rng(2 * nx + ny + nsrc)
+    vel = rng.uniform(1500.0, 4000.0, (nz, ny, nx)).astype(np.float32)
+    e = rng.uniform(0.0, 0.3, (nz, ny, nx)).astype(np.float32) if eta else None
+    sh = W.Shot(nx, ny, nz, w, 10.0, 10.0, 10.0, 5e-4, vel, eta=e, damping=damping, storage=storage.replace("sr", ""),
+                stochastic_round=storage.endswith("sr"), max_src=8, max_rec=70, max_steps=16)
+    for s in range(nsrc):
+        p = (nx // 2, ny // 2, nz // 2) if s % 3 == 0 else tuple(int(rng.integers(0, n)) for n in (nx, ny, nz))
+        sh.inject(*p, rng.standard_normal(16).astype(np.float32))
+    sh.record(np.stack([rng.integers(0, n, 70) for n in (nx, ny, nz)], axis=1))
+    for which in (W.WAVE_FIELD_U, W.WAVE_FIELD_UPREV):
+        sh.write(which, rng.standard_normal((nz, ny, nx)).astype(np.float32))
+    return sh
+
+
+@pytest.mark.parametrize("graph", [0, 2])
+@pytest.mark.parametrize("storage", ["bf16", "f16", "bf16sr"])
+def test_batch_of_streaming_16_bit_members(W, storage, graph):
+    say(f"case batch by size, streaming 16-bit members, {storage}, graph {graph}")
+    members = [m[:7] + (storage,) for m in STREAM16]
+    n = [3 + (5 * i) % 7 for i in range(len(members))]
+    b = W.Batch(storage=storage.replace("sr", ""), max_shots=len(members))
+    b.set_graph(graph)
+    shots = [_member(W, *m) for m in members]
+    for sh, k in zip(shots, n):
+        b.add(sh, k)
+    for k in (4, 1, 16):
+        b.run(k)
+    b.close()
+    for i, sh in enumerate(shots):
+        solo = _member(W, *members[i])
+        solo.set_kernel(W.WAVE_KERNEL_DIRECT)
+        solo.step(n[i])
+        for x, y in zip(_state(W, sh), _state(W, solo)):
+            assert np.isfinite(y).all() and np.array_equal(x, y), (i, members[i])
+
+
 @pytest.mark.parametrize("members", [MIXED, MANY, LARGE, HALF], ids=["mixed", "many", "large", "half"])
 def test_batch_runs_of_one_step(W, members):
     """Runs of one step, which launch more members together than longer ones and add

@@ -155,7 +155,9 @@ def test_runs_of_one_step_by_size(W):
                                                 (2500, 9, 1750, 0, "f32"), (1320, 33, 917, 0, "f32"),
                                                 (1900, 1320, 9, 0, "f32"), (1840, 1280, 17, 0, "f32"),
                                                 (3100, 2150, 9, 0, "bf16"),
-                                                (9, 1420, 1170, 4, "f32"), (16, 1060, 880, 8, "f32")])
+                                                (9, 1420, 1170, 4, "f32"), (16, 1060, 880, 8, "f32"),
+                                                (64, 945, 826, 20, "bf16"), (64, 945, 826, 20, "f16"),
+                                                (129, 666, 581, 20, "bf16"), (160, 598, 522, 20, "bf16")])
 def test_default_launch_of_thin_grids(W, nx, ny, nz, w, storage):
     """Few rows of tiles, one plane past whole layers of blocks, few columns: the
     default launch is not behind one workgroup per 64 x 8 streaming tile."""
