@@ -754,7 +754,10 @@ bool narrow_blocks(const SweepArgs& a) {
   return tiles == 3 || tiles == 5 || (tiles == 1 && (int64_t)a.ny * a.nz >= 4096);
 }
 
-// false: the grid does not fit the index arithmetic.
+// A launch holds less than 2^32 threads; a sixteenth of them is left for receivers.
+constexpr int64_t kLaunchThreads = 0xf0000000LL;
+
+// false: the grid does not fit the index arithmetic or one launch.
 bool block_grid(const SweepArgs& a, int tw, int ty, int zc, BlockGrid* g) {
   g->tiles_x = cdiv(a.nx, tw);
   g->tiles_y = cdiv(a.ny, ty);
@@ -780,7 +783,8 @@ bool block_grid(const SweepArgs& a, int tw, int ty, int zc, BlockGrid* g) {
   const bool runs = 25 * most > 27 * run || (zc == 4 && a.ny <= (tw == kTX && ty == kDY ? 112 : 160));
   const int64_t n = g->tiles_x * (runs ? run : (int64_t)g->slab * layers);
   if ((int64_t)(zc + 2 * kR) * a.plane * 4 > kWindowMax ||
-      n * std::max(g->tiles_x, g->slab) >= (int64_t(1) << 32) || n > 0x07ffffff ||
+      n * std::max(g->tiles_x, g->slab) >= (int64_t(1) << 32) ||
+      8 * n * (tw == kTX && ty == kDY && zc == kDZ ? 256 : tw * ty) > kLaunchThreads ||
       (runs && 8 * run * g->tiles_y >= (int64_t(1) << 32)))  // rows of blocks by layers
     return false;
   g->run = runs ? (int32_t)run : 0;
