@@ -154,7 +154,7 @@ __device__ __forceinline__ void block_rows(const SweepArgs& a, const StepIO& io,
   for (int k = 0; k < ZC; ++k) {
     vv[k] = NTP ? bld1_f32(rv, vo4, pl(k) * p4) : bld_f32(rv, vo4, pl(k) * p4);
     pv[k] = NTP ? S::bld1(rn, vo, pl(k) * pe) : S::bld(rn, vo, pl(k) * pe);
-    if (LAYER) ph[k] = NTP ? bld1_f32(rph, fo, pl(k) * p4) : bld_f32(rph, fo, pl(k) * p4);
+    if (LAYER) ph[k] = bld_f32(rph, fo, pl(k) * p4);
   }
   float er[ZC + 2], ex0[ZC], ex1[ZC], ey0[ZC], ey1[ZC];
   double tsc = 0.0, tz[ZC];
@@ -278,7 +278,7 @@ __device__ __forceinline__ void block_rows(const SweepArgs& a, const StepIO& io,
     for (int k = 0; k < ZC; ++k) {
       res[k] = q[kR + k] + n1[k];
       __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(n2[k]), rph,
-                                            (int)(FULL || k < nzb ? fo : kOOB), (int)(pl(k) * p4), kBst);
+                                            (int)(FULL || k < nzb ? fo : kOOB), (int)(pl(k) * p4), kStThrough);
     }
   }
 
@@ -347,6 +347,7 @@ __device__ __forceinline__ void duo_rows(const SweepArgs& a, const StepIO& io, D
   constexpr bool LAYER = EM != 0;
   constexpr int ZC = kDZ;
   static_assert(2 * kR * (kTX / 2) == NT && NXE <= NT, "one y-halo pair per thread and plane");
+  static_assert(sizeof(T) == 2 && !S::kSR && (EM == 0 || EM >= 2), "what duo_t launches");
 
   const int tid = threadIdx.x;
   const int col = 2 * (tid & 31), row = tid >> 5;
@@ -520,18 +521,11 @@ __device__ __forceinline__ void duo_rows(const SweepArgs& a, const StepIO& io, D
     }
   }
 
-  const uint32_t srkey = S::kSR ? pcg_hash((uint32_t)a.step) : 0u;
   T ev[ZC][2];
 #pragma unroll
   for (int k = 0; k < ZC; ++k) {
-    if constexpr (S::kSR) {  // x is even: both points take their bits from one word
-      const uint32_t wd = sr_word(srkey, a.nx, a.ny, x, y, b.zb + k);
-      ev[k][0] = f32_to_bf16_sr(res[k][0], wd);
-      ev[k][1] = f32_to_bf16_sr(res[k][1], wd >> 16);
-    } else {
-      ev[k][0] = S::enc(res[k][0]);
-      ev[k][1] = S::enc(res[k][1]);
-    }
+    ev[k][0] = S::enc(res[k][0]);
+    ev[k][1] = S::enc(res[k][1]);
   }
   if (smask) {
 #pragma unroll
@@ -549,13 +543,9 @@ __device__ __forceinline__ void duo_rows(const SweepArgs& a, const StepIO& io, D
   for (int k = 0; k < ZC; ++k) {
     const int so = (int)(pl(k) * pe), vk = (int)(FULL || k < nzb ? vo : kOOB);
     const T e1 = valid1 ? ev[k][1] : (T)0;
-    if constexpr (sizeof(T) == 4)
-      __builtin_amdgcn_raw_buffer_store_b64(
-          u32x2{__builtin_bit_cast(uint32_t, ev[k][0]), __builtin_bit_cast(uint32_t, e1)}, rn, vk, so, kStThrough);
-    else
-      __builtin_amdgcn_raw_buffer_store_b32(
-          (uint32_t)__builtin_bit_cast(uint16_t, ev[k][0]) | ((uint32_t)__builtin_bit_cast(uint16_t, e1) << 16),
-          rn, vk, so, kStThrough);
+    __builtin_amdgcn_raw_buffer_store_b32(
+        (uint32_t)__builtin_bit_cast(uint16_t, ev[k][0]) | ((uint32_t)__builtin_bit_cast(uint16_t, e1) << 16),
+        rn, vk, so, kStThrough);
   }
 }
 
@@ -592,6 +582,7 @@ __device__ __forceinline__ void block_sweep(const SweepArgs& a, const StepIO& io
   int tx, ty, zl;
   if (!block_at(g, xcd, at, &tx, &ty, &zl)) return;
   constexpr bool damp = LM != 0;
+  static_assert(!(NTP && damp), "larger states with a layer run the streaming kernels");
   const ChunkInfo c = chunk_of(zl, a.nz, a.w, ZC, damp);
   BlockAt b;
   b.x0 = tx * TW;
