@@ -71,7 +71,9 @@ def describe(cfg) -> str:
     if v == 9:
         return f"stream, x neighbours by wavefront shuffles, 64x{nw} zchunk={zc}"
     if v == 10:
-        return f"blocks of 64x{nw}x{zc} points"
+        if (nw, zc) == (4, 4):
+            return "blocks of 64x4x4 points, or 32x8x4 by the grid's width"
+        return f"blocks of 64x{nw}x{zc} points" + (", two points per lane" if zc == 4 else "")
     if v in (4, 5):
         return f"2.5-D {'ring of 9 LDS planes' if v == 4 else 'LDS plane + shifted registers'} " \
                f"64x{nw} zchunk={zc}"

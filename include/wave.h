@@ -218,10 +218,12 @@ int64_t wave_step_count(const wave_ctx *ctx);
 
 /* Copy a field to a host float array [nz][ny][nx] (16-bit storage is
  * widened exactly).  Synchronises.  The copy goes through a pinned host
- * buffer of at most 64 MB (or one padded plane, if larger), allocated and
- * freed by the call.  Errors: EINVAL; EDEVICE when a copy fails (sticky,
- * as for every device error) or no pinned memory is left for the buffer
- * (not sticky). */
+ * buffer of at most 64 MB (or one padded plane, if larger).  One of up to 16 MB
+ * (2^24 bytes) stays with the context, for wave_write_field too, until wave_free,
+ * so 64 contexts that have read a field may hold 1 GB of pinned memory; a larger
+ * one is allocated and freed by the call.  Errors: EINVAL; EDEVICE when a copy
+ * fails (sticky, as for every device error) or no pinned memory is left for the
+ * buffer (not sticky). */
 int wave_read_field(wave_ctx *ctx, int32_t which, float *host_out);
 
 /* Overwrite u^n, u^{n-1} or phi^n from a host float array [nz][ny][nx]

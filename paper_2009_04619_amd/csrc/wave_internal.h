@@ -247,9 +247,11 @@ int64_t sweep_footprint(int nx, int ny, int nz, int w, bool damping, bool eta_ar
 // against 95; 384 x 320 x 300, 347 MB, 97 against 105; 352^3, 415 MB, 123 against
 // 117).  16-bit storage takes two points per lane from 10 MB on (bf16 64^3 5.2
 // against 4.5 with one, 128 x 112 x 96 7.2 against 7.9, 256^3 42 against 50, 320^3
-// 84 against 93; without a layer 256^3 27.7 against 36.4).  Without a layer,
-// larger grids take 8 x 8 blocks (float32 256^3 40 against 41 with 4 x 4, 384^3 137
-// against 151 streaming, 600^3 659 against 685; bf16 512^3 220 against 221).
+// 84 against 93; without a layer 256^3 27.7 against 36.4).  Without a layer
+// and stochastic rounding, states from 240 MB (16-bit ones from 280 MB) take 8 x 8
+// blocks (float32 272^3, 241 MB, 54.0 against 51.1 with 4 x 4, 280^3 57.3 against 58.4,
+// 300^3 75.8 against 81.0 and 85.0 streaming, 384^3 137 against 151, 600^3 659 against
+// 685; bf16 336^3, 303 MB, 78 against 83 streaming, 512^3 247 against 230).
 void block_default(const SweepArgs& a, int storage, int* ty, int* zc);
 hipError_t launch_sweep_block(const SweepArgs& a, const StepIO& io, int storage, int ty, int zc,
                               hipStream_t s);
