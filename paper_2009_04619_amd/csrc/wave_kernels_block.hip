@@ -18,10 +18,10 @@
 // the receivers of the step before, which saves the second launch.
 //
 // us per step with a source and a receiver line, before (64 x 8 streaming
-// tiles) -> now: 64^3 22.5 -> 4.1, 128^3 23.4 -> 9.2, 160^3 29.5 -> 15, 192^3 35.9
-// -> 24, 256^3 65.0 -> 55 (20-cell layer; 16 at 64^3); 256^3 without a layer 50.1
+// tiles) -> now: 64^3 22.5 -> 4.0, 128^3 23.4 -> 9.2, 160^3 29.5 -> 14.5, 192^3 35.9
+// -> 24.5, 256^3 65.0 -> 55 (20-cell layer; 16 at 64^3); 256^3 without a layer 50.1
 // -> 40 (7.2 TB/s of its algorithmic bytes on a zero field; a copy inside that
-// cache moves 8.3).  bf16 with two points per lane: 128^3 23.5 -> 8.2, 256^3 57 ->
+// cache moves 8.3).  bf16 with two points per lane: 128^3 23.5 -> 7.4, 256^3 57 ->
 // 42.
 //
 // What bounds it now: up to about 96^3 the launch itself (2.5 us) and one pass of
@@ -250,6 +250,9 @@ __device__ __forceinline__ void block_rows(const SweepArgs& a, const StepIO& io,
     }
   }
   if (LAYER) {
+    // Zeros count as small, so ahead of the wavefront, where all is zero, the plain
+    // divisions run; such steps are not the slower ones (us per step of shots from rest
+    // and in flight: 192^3 21.9 and 24.7, 256^3 54.3 and 54.9, bf16 160^3 15.0 and 14.7).
     float least = __builtin_fminf(__builtin_fabsf(n1[0]), __builtin_fabsf(n2[0]));
 #pragma unroll
     for (int k = 1; k < ZC; ++k)

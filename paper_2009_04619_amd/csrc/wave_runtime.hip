@@ -2217,7 +2217,8 @@ int wave_batch_tune(wave_batch* b, int32_t trial_steps, int32_t chosen[2]) {
   if (rc != WAVE_OK) return leave(rc);
   for (const auto& sh : shapes) {
     const bool by_size = sh[0] == 4;
-    const int32_t head = by_size ? 4 : 1, tail = by_size ? std::max(8, trial_steps) : trial_steps;
+    const int32_t trial = std::min(trial_steps, 1 << 30);   // head + trial stays an int32_t
+    const int32_t head = by_size ? 4 : 1, tail = by_size ? std::max(8, trial) : trial;
     double t1 = 0.0, u1 = 0.0, t2 = 0.0, u2 = 0.0;
     rc = wave_batch_set_kernel(b, sh[0], sh[1]);
     if (rc == WAVE_OK) rc = wave_batch_run(b, 1);

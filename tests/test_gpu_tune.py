@@ -118,11 +118,12 @@ def test_tuning_a_batch_keeps_its_speed(W, storage):
     assert max(tuned) < 1.06 * by_size, (storage, cfgs, tuned, by_size)
 
 
-def test_members_without_steps_end_the_trials(W):
+@pytest.mark.parametrize("trial", [3, 2 ** 31 - 1])
+def test_members_without_steps_end_the_trials(W, trial):
     """A shape that no step is left for is not the fastest."""
-    say("case tuner without steps")
+    say(f"case tuner without steps, {trial}")
     b, shots = batch(W, sizes(3, 30, 50, 2), 6)
-    assert tuple(b.tune(3)) == (4, 4)
+    assert tuple(b.tune(trial)) == (4, 4)
     assert all(b.remaining(sh) == 0 for sh in shots)
     b.close()
     for sh in shots:
