@@ -475,14 +475,14 @@ int wave_batch_remaining(const wave_batch *b, const wave_ctx *ctx, int32_t *rema
  * holds an eta array, and such a member cannot join then), and the number of
  * steps captured into one graph (0 = plain launches).  A batch starts without
  * a set tile, and (4, 4) returns to that: each member's sweep is then chosen by
- * its size.  Members that run WAVE_KERNEL_BLOCK by default, with at most 4
- * sources, run it here; the others 64 x 8 tiles, or 128 x 8 with two points per
- * lane (16-bit storage, no eta array, no stochastic rounding, neither up to 64 nor
- * from 129 to 192 columns).  Block-kernel
- * members whose states together fit the memory-side cache take their steps of a
- * run together, one group of members after the other (a run of one step takes as
- * many as a launch holds); their launches are never captured, and need no second
- * launch per step for sources and receivers. */
+ * its size.  Members that run WAVE_KERNEL_BLOCK by default run it here; the
+ * others 64 x 8 tiles, or 128 x 8 with two points per lane (16-bit storage, no
+ * eta array, no stochastic rounding, neither up to 64 nor from 129 to 192
+ * columns).  Block-kernel members whose states together fit the memory-side
+ * cache take their steps of a run together, one group of members after the other
+ * (a run of one step takes as many as a launch holds); their launches are never
+ * captured, and need no second launch per step for sources and receivers unless a
+ * member of the group has more than 4 sources. */
 int wave_batch_set_kernel(wave_batch *b, int32_t rows_per_wave, int32_t waves_per_group);
 int wave_batch_set_graph(wave_batch *b, int32_t steps_per_graph);
 

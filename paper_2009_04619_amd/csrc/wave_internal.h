@@ -229,7 +229,8 @@ hipError_t launch_sweep_batch_pair(const BatchShot* shots, BatchState* state, in
 bool block_config_supported(int ty, int zc, const SweepArgs& a, int storage);
 // The same for several members of a batch, 4 x 4 blocks, or (duo) 8 x 4.  block_batch_grid sizes
 // a member's share of a launch (workgroups; a multiple of 8).  All members of a
-// launch share lm: 0 damping off, 1 eta array, 2 tables.  launch_record_last samples
+// launch share lm: 0 damping off, 1 eta array, 2 tables, and among these members with
+// damping off whose table entry has layer width 0.  launch_record_last samples
 // the receivers of the last step of the first n members of the tables, which must
 // hold their states at the start of the run.
 int block_batch_grid(const SweepArgs& a, bool duo, int nrec, BlockGrid* g);

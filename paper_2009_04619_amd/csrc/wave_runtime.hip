@@ -606,9 +606,10 @@ struct wave_batch {
 // step, before the next group starts.  Block groups come first.
 struct wave_batch::Group {
   int first, count;
-  bool block;                 // the block kernel (lm: 0 damping off, 1 eta array, 2 tables)
-  int lm;
-  bool duo;                   // two points per lane (8 x 4 blocks)
+  bool block;                 // the block kernel
+  bool duo;                   // with two points per lane (8 x 4 blocks)
+  bool apart;                 // a member has more sources than a sweep launch takes: a
+                              // launch of their own for sources and receivers
   int ry, nw;                 // otherwise the streaming tile (ry 0: two points per lane)
   bool eta_any;               // some member holds a per-point eta array
   std::vector<int64_t> prefix;        // streaming: workgroups of the first k members
@@ -725,24 +726,29 @@ void batch_drop_graphs(wave_batch* b) {
 }
 
 // Whether a member of a batch without a set tile runs the block kernel: its
-// own default launch does, and its sources fit one launch.  *duo: with two
-// points per lane.
+// own default launch does.  *duo: with two points per lane.
 bool batch_block_member(const wave_ctx* c, bool* duo) {
   int ty, zc;
   const wave::SweepArgs a = sweep_args(c);
   wave::block_default(a, kernel_storage(&c->d), &ty, &zc);
   wave::BlockGrid g;
   *duo = ty == 8 && zc == 4;
-  return ty > 0 && c->nsrc <= wave::kStepSrc && (*duo || member_bytes(c) <= 280 * 1000000LL) &&
+  return ty > 0 && (*duo || member_bytes(c) <= 280 * 1000000LL) &&
          wave::block_batch_grid(a, *duo, c->nrec, &g) > 0;
 }
 
 // Launch order of a member in a batch without a set tile: members of one kind
-// can share a launch.  Streaming kinds: two points per lane, one, one with an eta
-// array.
+// can share a launch.  Block kinds: damping off, an eta array, tables, and these with
+// two points per lane.  Members of little state count as tables with damping off too
+// (batch_layout clears the layer's width for their blocks): their steps are as long as
+// a launch, and each kind is one more launch (8 members of 14-45 cells of every kind,
+// us a step: 37.7 with a kind of their own and many-source members streaming, 17.6
+// now; 38.9 in 64 x 16 tiles).  Streaming kinds: two points per lane, one, one with
+// an eta array.
 constexpr int kStreamKind = 6;
+constexpr int64_t kSmallBytes = 10 * 1000000LL;
 int batch_kind(const wave_ctx* c) {
-  const int lm = !c->damp ? 0 : eta_array(&c->d) ? 1 : 2;
+  const int lm = eta_array(&c->d) ? 1 : c->damp || member_bytes(c) < kSmallBytes ? 2 : 0;
   bool duo = false;
   if (batch_block_member(c, &duo)) return lm + (duo ? 3 : 0);
   if (lm == 1) return kStreamKind + 2;
@@ -777,8 +783,8 @@ void batch_layout(wave_batch* b) {
       g.first = (int)i;
       g.count = 0;
       g.block = block;
-      g.lm = kind % 3;
       g.duo = kind >= 3;
+      g.apart = false;
       g.ry = b->ry;
       g.nw = b->nw;
       if (b->by_size) {
@@ -803,6 +809,8 @@ void batch_layout(wave_batch* b) {
     e.target = 0;
     e.inj = inject_args(c);
     if (g.block) {
+      if (!c->damp) e.sa.w = 0;
+      g.apart = g.apart || c->nsrc > wave::kStepSrc;
       b->nwg[i] = wave::block_batch_grid(e.sa, g.duo, c->nrec, &b->grid[i]);
       continue;
     }
@@ -883,15 +891,20 @@ hipError_t batch_run_stream(wave_batch* b, int group) {
 // All steps of block members first .. first + count - 1 (of one kind), one launch
 // each: what changes from step to step travels in the launch's arguments, so these
 // are never captured.  The sources of a step and the receivers of the step before
-// go with it, unless the caller sees to them (`alone`, one step).
-hipError_t batch_run_block(wave_batch* b, int first, int count, int lm, bool duo, bool alone) {
+// go with it, or (kApart) both follow it in a launch of their own, or (kNone) the
+// caller sees to them.
+enum class BlockIO { kWith, kApart, kNone };
+hipError_t batch_run_block(wave_batch* b, int first, int count, bool duo, BlockIO how) {
   const wave::BatchShot* h = b->h_shots.data() + first;
   wave::BlockBatch bb;
   memset(&bb, 0, sizeof(bb));
+  int lm = 0;
   for (int i = 0; i < count; ++i) {
+    const wave_ctx* c = b->members[first + i];
     bb.m[i].g = b->grid[first + i];
-    bb.m[i].io = alone ? no_sources() : step_sources(b->members[first + i]);
+    bb.m[i].io = how == BlockIO::kWith ? step_sources(c) : no_sources();
     bb.begin[i + 1] = bb.begin[i] + b->nwg[first + i];
+    if (c->damp) lm = eta_array(&c->d) ? 1 : 2;
   }
   int k = count;
   for (int32_t t = 0; t < h[0].target; ++t) {
@@ -902,7 +915,7 @@ hipError_t batch_run_block(wave_batch* b, int first, int count, int lm, bool duo
       m.cur = (c->icur < c->iprev ? 0 : 1) ^ (t & 1);
       m.step = (int32_t)c->step + t;
       step_samples(c, c->step + t, &m.io);
-      step_receivers(c, t > 0, c->trace_count + t - 1, &m.io);
+      step_receivers(c, how == BlockIO::kWith && t > 0, c->trace_count + t - 1, &m.io);
     }
     bb.n = k;
     bb.back = t & 1;
@@ -916,6 +929,8 @@ hipError_t batch_run_block(wave_batch* b, int first, int count, int lm, bool duo
     } else {
       e = wave::launch_sweep_block_batch(b->d_shots + first, bb, b->kstore, lm, duo, b->stream);
     }
+    if (e == hipSuccess && how == BlockIO::kApart)
+      e = wave::launch_inject_batch(b->d_shots + first, b->d_state + first, k, b->kstore, b->stream);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -928,12 +943,22 @@ hipError_t batch_run_blocks(wave_batch* b, int32_t steps) {
   for (; ng < b->groups.size() && b->groups[ng].block; ++ng) n += b->groups[ng].count;
   if (n == 0) return hipSuccess;
   if (steps > 1 || ng == 1 || b->tuning) {
-    for (size_t i = 0; i < ng; ++i) {
+    hipError_t e = hipSuccess;
+    for (size_t i = 0; i < ng && e == hipSuccess; ++i) {
       const wave_batch::Group& g = b->groups[i];
-      const hipError_t e = batch_run_block(b, g.first, g.count, g.lm, g.duo, false);
-      if (e != hipSuccess) return e;
+      e = batch_run_block(b, g.first, g.count, g.duo, g.apart ? BlockIO::kApart : BlockIO::kWith);
     }
-    return wave::launch_record_last(b->d_shots, b->d_state, n, b->kstore, b->stream);
+    // the others' last receivers: runs of groups that are not apart
+    for (size_t i = 0; i < ng && e == hipSuccess;) {
+      size_t j = i;
+      int count = 0;
+      for (; j < ng && b->groups[j].apart == b->groups[i].apart; ++j) count += b->groups[j].count;
+      const int first = b->groups[i].first;
+      if (!b->groups[i].apart)
+        e = wave::launch_record_last(b->d_shots + first, b->d_state + first, count, b->kstore, b->stream);
+      i = j;
+    }
+    return e;
   }
   // a run of one step comes back to no member's state: as many members to a launch
   // as it takes, and one launch for all sources and receivers (24 float32 shots of
@@ -941,11 +966,12 @@ hipError_t batch_run_blocks(wave_batch* b, int32_t steps) {
   // together 902; 128 shots of 24-40 cells 150, 132, 143)
   for (size_t i = 0; i < ng;) {
     size_t j = i + 1;
-    while (j < ng && b->groups[j].lm == b->groups[i].lm && b->groups[j].duo == b->groups[i].duo) ++j;
+    const int kind = batch_kind(b->members[b->groups[i].first]);
+    while (j < ng && batch_kind(b->members[b->groups[j].first]) == kind) ++j;
     const int end = b->groups[j - 1].first + b->groups[j - 1].count;
     for (int m = b->groups[i].first; m < end; m += wave::kBlockMembers) {
       const hipError_t e = batch_run_block(b, m, std::min(wave::kBlockMembers, end - m),
-                                           b->groups[i].lm, b->groups[i].duo, true);
+                                           b->groups[i].duo, BlockIO::kNone);
       if (e != hipSuccess) return e;
     }
     i = j;

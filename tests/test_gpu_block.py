@@ -207,9 +207,9 @@ def test_block_tile_widths(W, nx, storage):
         assert np.array_equal(got[key], expect[key]), (nx, storage, key)
 
 
-# 16-bit members that stream: two points per lane, one where 128-wide tiles leave half of
-# them idle, and one with an eta array; among them members of the block kernel
-STREAM16 = [(100, 40, 30, 4, 6, False, True, "bf16"), (60, 40, 30, 4, 6, False, True, "bf16"),
+# 16-bit members with more sources than a sweep launch takes, among others: damping off,
+# tables and an eta array
+SOURCES16 = [(100, 40, 30, 4, 6, False, True, "bf16"), (60, 40, 30, 4, 6, False, True, "bf16"),
             (131, 30, 26, 4, 5, False, True, "bf16"), (64, 33, 20, 0, 7, False, False, "bf16"),
             (70, 30, 30, 4, 5, True, True, "bf16"), (200, 24, 22, 4, 5, False, True, "bf16"),
             (50, 30, 30, 4, 2, False, True, "bf16")]
@@ -233,9 +233,9 @@ def _member(W, nx, ny, nz, w, nsrc, eta, damping, storage):
 
 @pytest.mark.parametrize("graph", [0, 2])
 @pytest.mark.parametrize("storage", ["bf16", "f16", "bf16sr"])
-def test_batch_of_streaming_16_bit_members(W, storage, graph):
-    say(f"case batch by size, streaming 16-bit members, {storage}, graph {graph}")
-    members = [m[:7] + (storage,) for m in STREAM16]
+def test_batch_of_16_bit_members_with_many_sources(W, storage, graph):
+    say(f"case batch by size, 16-bit members with many sources, {storage}, graph {graph}")
+    members = [m[:7] + (storage,) for m in SOURCES16]
     n = [3 + (5 * i) % 7 for i in range(len(members))]
     b = W.Batch(storage=storage.replace("sr", ""), max_shots=len(members))
     b.set_graph(graph)

@@ -221,3 +221,50 @@ def test_membership_and_streams(W, tile, graph):
     for i, sh in enumerate(m):
         same(end(W, sh), solo_steps(W, i, "f32", total[i]), (tile, i))
     b.close()
+
+
+@pytest.mark.parametrize("storage,grids", [("bf16", [(395, 352, 331, 20, False), (163, 585, 570, 20, False),
+                                                     (300, 300, 300, 20, True)]),
+                                           ("f16", [(384, 360, 331, 20, False)]), ("f32", [(300, 300, 290, 20, False)])])
+def test_batch_of_streaming_members(W, storage, grids):
+    """Members past the block kernel's sizes without a set tile: two points per lane,
+    one where 128-wide tiles leave a third of the lanes idle, one with an eta array,
+    beside small ones, in captured steps and plain ones."""
+    say(f"case batch of streaming members {storage}")
+    specs = [(g[:4], g[4]) for g in grids] + [((60, 44, 30, 4), False), ((70, 30, 30, 4), True)]
+    n = [3, 5, 4, 5, 2]
+    b = W.Batch(storage=storage, max_shots=len(specs))
+    b.set_graph(2)
+    shots = [make(W, *g, storage, True, eta, 2, seed=i) for i, (g, eta) in enumerate(specs)]
+    for sh, k in zip(shots, n):
+        b.add(sh, k)
+    b.run(3)
+    b.run(2)
+    b.close()
+    for i, (g, eta) in enumerate(specs):
+        solo = make(W, *g, storage, True, eta, 2, seed=i)
+        solo.set_kernel(*DIRECT)
+        solo.step(n[i])
+        same(end(W, shots[i]), end(W, solo), (storage, i))
+
+
+def test_small_members_of_every_kind(W):
+    """Small members with damping off share launches with those that have a layer: a
+    layer width that the flag switches off among them."""
+    say("case small members of every kind")
+    specs = [(70, 45, 37, 5, True, False, 1), (64, 40, 36, 0, False, False, 2), (33, 50, 41, 8, False, False, 1),
+             (90, 30, 30, 6, True, True, 1), (50, 50, 50, 9, True, False, 6), (48, 33, 20, 0, False, False, 7)]
+    for pieces in ((1, 1, 2, 4, 9), (12,)):
+        n = [5, 9, 12, 7, 10, 3]
+        b = W.Batch(max_shots=8)
+        shots = [make(W, *m[:4], "f32", m[4], m[5], m[6], seed=i) for i, m in enumerate(specs)]
+        for sh, k in zip(shots, n):
+            b.add(sh, k)
+        for k in pieces:
+            b.run(k)
+        b.close()
+        for i, m in enumerate(specs):
+            solo = make(W, *m[:4], "f32", m[4], m[5], m[6], seed=i)
+            solo.set_kernel(*DIRECT)
+            solo.step(n[i])
+            same(end(W, shots[i]), end(W, solo), (pieces, i))

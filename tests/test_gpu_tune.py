@@ -171,3 +171,37 @@ def test_default_launch_of_thin_grids(W, nx, ny, nz, w, storage):
     other.close()
     say(f"default {default:.1f}, 64 x 8 tiles {stream:.1f} us a step")
     assert default < 1.05 * stream
+
+
+@pytest.mark.parametrize("piece", [1, 5, 30])
+def test_small_members_of_every_kind_by_size(W, piece):
+    """Tables, eta arrays, damping off and many sources side by side: without a set tile
+    they cost no more than the 64 x 16 tiles, which take them in one launch."""
+    say(f"case batch of every kind, {piece} steps a run")
+    shots = []
+    for i, (nx, ny, nz) in enumerate(sizes(8, 14, 45, 4)):
+        kind = i % 4
+        eta = np.full((nz, ny, nx), 0.1, np.float32) if kind == 1 else None
+        rng = np.random.default_rng(i)
+        sh = W.Shot(nx, ny, nz, 7, 10.0, 10.0, 10.0, 5e-4, np.full((nz, ny, nx), 2500.0, np.float32), eta=eta,
+                    damping=kind != 2, max_src=6, max_rec=8, max_steps=3000)
+        for s in range(6 if kind == 3 else 1):
+            sh.inject(nx // 2, ny // 2, nz // 2 + s, rng.standard_normal(8).astype(np.float32))
+        sh.record(np.array([[j, ny // 2, nz // 2] for j in range(8)], np.int32))
+        shots.append(sh)
+    b = W.Batch(max_shots=len(shots))
+    for sh in shots:
+        b.add(sh, 3000)
+
+    def under(cfg):
+        def run(n):
+            b.set_kernel(*cfg)
+            for _ in range(-(-n // piece)):
+                b.run(piece)
+        return run, b.stream
+    by_size, tile = least_us([under((4, 4)), under((1, 16))], 30, reps=8)
+    b.close()
+    for sh in shots:
+        sh.close()
+    say(f"by size {by_size:.1f}, 64 x 16 tiles {tile:.1f} us a step")
+    assert by_size < 1.04 * tile
