@@ -163,12 +163,16 @@ def test_default_launch_of_thin_grids(W, nx, ny, nz, w, storage):
     """Few rows of tiles, one plane past whole layers of blocks, few columns: the
     default launch is not behind one workgroup per 64 x 8 streaming tile."""
     say(f"case thin {nx}x{ny}x{nz} {storage}")
-    sh = shot(W, nx, ny, nz, w, 2000, storage, damping=w > 0)
-    other = shot(W, nx, ny, nz, w, 2000, storage, damping=w > 0)
-    other.set_kernel(1, 1, 8, 0)
-    default, stream = least_us([(sh.step, sh.stream), (other.step, other.stream)], 20, reps=4)
-    sh.close()
-    other.close()
+    best = [np.inf, np.inf]
+    for order in ((0, 1), (1, 0)):      # where the arenas lie in memory weighs a few percent: each side has both
+        sh = [None, None]
+        for q in order:
+            sh[q] = shot(W, nx, ny, nz, w, 2000, storage, damping=w > 0)
+        sh[1].set_kernel(1, 1, 8, 0)
+        best = np.minimum(best, least_us([(x.step, x.stream) for x in sh], 20, reps=4))
+        for q in order:
+            sh[q].close()
+    default, stream = best
     say(f"default {default:.1f}, 64 x 8 tiles {stream:.1f} us a step")
     assert default < 1.05 * stream
 
